@@ -2,16 +2,10 @@
 // (I - h gamma J) x = b, for every state of a batch (gfx950).
 //
 //  form      : A = I - h gamma J, transposed from the element-major,
-//              state-fastest Jacobian into one contiguous row-major N x N
+//              state-fastest Jacobian into one contiguous column-major N x N
 //              matrix per state (FP64 or FP32), through an LDS tile so both
 //              the reads and the writes are coalesced.
-//  lu        : one workgroup per state; right-looking LU with partial
-//              pivoting in panels of 16 columns.  The panel is factored in
-//              LDS, the row interchanges are applied to the other columns,
-//              U12 = L11^-1 A12 is formed in LDS and the trailing matrix is
-//              updated with 16x16x4 matrix-core instructions (FP32 or FP64).
-//  solve     : one wavefront per state; P b, unit-lower and upper
-//              triangular solves by row dot products.
+//  lu, solve : newton_blocked.hip.
 //  residual  : r = b - (I - h gamma J) x in FP64, one thread per state,
 //              straight from the state-fastest Jacobian (coalesced).
 // Mode 1 (mixed) factors in FP32, refines in FP64 and re-solves the states
@@ -27,6 +21,7 @@
 #include <utility>
 
 #include "../../include/pyjac.h"
+#include "newton_blocked.hpp"
 #include "tables.hpp"
 
 namespace pyjac {
@@ -35,14 +30,6 @@ int mech_device(const pyjac_mech* m);
 int mech_species(const pyjac_mech* m);
 
 namespace {
-
-constexpr int NB = 16;           // panel width
-constexpr int LU_THREADS = 256;  // 4 wavefronts per state
-constexpr int ST_UNSET = -100;   // internal per-state status before convergence
-constexpr int ST_SING32 = -4;    // zero pivot in the FP32 factor: re-solved in FP64
-
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef double doublex4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------- form
 // grid: (ceil(n/16), ceil(N*N/64)); 256 threads: tile of 64 elements x 16 states
@@ -65,11 +52,11 @@ __global__ __launch_bounds__(256) void form_kernel(int N, int64_t n, int64_t ld,
     const int64_t st = ok ? (list ? list[slot] : slot) : 0;
     const double hg = ok ? h[st] * gamma : 0.0;
     for (int r = tid / 16; r < 64; r += 16) {
-      const int64_t e = e0 + r;
+      const int64_t e = e0 + r;                  // position in the column-major matrix
       T v = T(0);
       if (ok && e < NN) {
-        const double jv = jac[e * ld + st];
-        const int64_t i = e / N, j = e % N;
+        const int64_t j = e / N, i = e % N;
+        const double jv = jac[(i * N + j) * ld + st];
         const double a = (i == j ? 1.0 : 0.0) - hg * jv;
         if (!isfinite(a)) status[st] = -3;
         v = (T)a;
@@ -78,7 +65,7 @@ __global__ __launch_bounds__(256) void form_kernel(int N, int64_t n, int64_t ld,
     }
   }
   __syncthreads();
-  // store: lanes element-fastest, one contiguous row-major matrix per state
+  // store: lanes element-fastest, one contiguous column-major matrix per state
   {
     const int r = tid % 64;
     for (int s = tid / 64; s < 16; s += 4) {
@@ -86,160 +73,6 @@ __global__ __launch_bounds__(256) void form_kernel(int N, int64_t n, int64_t ld,
       if (slot < lim && e < NN) A[slot * NN + e] = tile[r][s];
     }
   }
-}
-
-template <typename T> struct Mfma;
-// 16x16x4 matrix-core products.  Both precisions take A[row = lane % 16][k =
-// lane / 16] and B[k = lane / 16][col = lane % 16]; the result slot v of lane
-// l holds column l % 16 and row row(l / 16, v), which differs between the FP32
-// and the FP64 instruction (checked on gfx950 with one-hot operands).
-template <> struct Mfma<float> {
-  typedef floatx4 acc_t;
-  __device__ static acc_t run(float a, float b, acc_t c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-  __device__ static int row(int q, int v) { return 4 * q + v; }
-};
-template <> struct Mfma<double> {
-  typedef doublex4 acc_t;
-  __device__ static acc_t run(double a, double b, acc_t c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
-  __device__ static int row(int q, int v) { return q + 4 * v; }
-};
-
-// ---------------------------------------------------------------- LU
-// One workgroup per (listed) state.  A: row-major N x N per slot; piv: N per slot.
-// LDS: panel Pn[N][NB+1], U12 U[NB][N+1], reduction scratch.
-template <typename T>
-__global__ __launch_bounds__(LU_THREADS) void lu_kernel(int N, int64_t n, T* __restrict__ Aall,
-                                                        int* __restrict__ pivall, const int* __restrict__ list,
-                                                        const int* __restrict__ count, int* __restrict__ status,
-                                                        int sing_code) {
-  extern __shared__ char smem[];
-  const int64_t slot = blockIdx.x;
-  const int64_t lim = count ? *count : n;
-  if (slot >= lim) return;
-  const int64_t st = list ? list[slot] : slot;
-  if (status[st] == -3) return;
-  T* A = Aall + slot * (int64_t)N * N;
-  int* piv = pivall + slot * (int64_t)N;
-  const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
-  const int PS = NB + 1, US = N + 1;
-  T* Pn = reinterpret_cast<T*>(smem);                       // N * PS
-  T* U = Pn + (size_t)N * PS;                               // NB * US
-  T* redv = U + (size_t)NB * US;                            // LU_THREADS
-  int* redi = reinterpret_cast<int*>(redv + LU_THREADS);    // LU_THREADS
-  __shared__ int singular;
-  if (tid == 0) singular = 0;
-  for (int k0 = 0; k0 < N; k0 += NB) {
-    const int nb = min(NB, N - k0), M = N - k0, W = N - k0 - nb;
-    // 1. panel to LDS
-    for (int e = tid; e < M * nb; e += LU_THREADS) {
-      const int r = e / nb, c = e % nb;
-      Pn[r * PS + c] = A[(int64_t)(k0 + r) * N + k0 + c];
-    }
-    __syncthreads();
-    // 2. factor the panel with partial pivoting
-    for (int c = 0; c < nb; ++c) {
-      T best = T(-1);
-      int bi = c;
-      for (int r = c + tid; r < M; r += LU_THREADS) {
-        const T v = fabs(Pn[r * PS + c]);
-        if (v > best) { best = v; bi = r; }
-      }
-      redv[tid] = best;
-      redi[tid] = bi;
-      __syncthreads();
-      for (int w = LU_THREADS / 2; w > 0; w >>= 1) {
-        if (tid < w) {
-          const T a = redv[tid], b = redv[tid + w];
-          const int ia = redi[tid], ib = redi[tid + w];
-          if (b > a || (b == a && ib < ia)) { redv[tid] = b; redi[tid] = ib; }
-        }
-        __syncthreads();
-      }
-      const int pr = redi[0];
-      const T pmax = redv[0];
-      if (tid == 0) {
-        piv[k0 + c] = k0 + pr;
-        if (!(pmax > T(0))) singular = 1;
-      }
-      if (pr != c && tid < nb) {
-        const T t = Pn[c * PS + tid];
-        Pn[c * PS + tid] = Pn[pr * PS + tid];
-        Pn[pr * PS + tid] = t;
-      }
-      __syncthreads();
-      const T d = Pn[c * PS + c];
-      const T inv = d != T(0) ? T(1) / d : T(0);
-      for (int r = c + 1 + tid; r < M; r += LU_THREADS) {
-        const T l = Pn[r * PS + c] * inv;
-        Pn[r * PS + c] = l;
-        for (int cc = c + 1; cc < nb; ++cc) Pn[r * PS + cc] -= l * Pn[c * PS + cc];
-      }
-      __syncthreads();
-    }
-    // 3. panel back to global
-    for (int e = tid; e < M * nb; e += LU_THREADS) {
-      const int r = e / nb, c = e % nb;
-      A[(int64_t)(k0 + r) * N + k0 + c] = Pn[r * PS + c];
-    }
-    // 4. row interchanges on the columns outside the panel (sequential in c)
-    for (int c = 0; c < nb; ++c) {
-      const int pr = piv[k0 + c];
-      if (pr != k0 + c) {
-        for (int col = tid; col < N - nb; col += LU_THREADS) {
-          const int cc = col < k0 ? col : col + nb;
-          const T t = A[(int64_t)(k0 + c) * N + cc];
-          A[(int64_t)(k0 + c) * N + cc] = A[(int64_t)pr * N + cc];
-          A[(int64_t)pr * N + cc] = t;
-        }
-      }
-      __syncthreads();
-    }
-    if (W <= 0) break;
-    // 5. U12 = L11^-1 A12 (unit lower), in LDS, then back to global
-    for (int e = tid; e < nb * W; e += LU_THREADS) {
-      const int r = e / W, c = e % W;
-      U[r * US + c] = A[(int64_t)(k0 + r) * N + k0 + nb + c];
-    }
-    __syncthreads();
-    for (int c = tid; c < W; c += LU_THREADS) {
-      for (int r = 1; r < nb; ++r) {
-        T acc = U[r * US + c];
-        for (int t = 0; t < r; ++t) acc -= Pn[r * PS + t] * U[t * US + c];
-        U[r * US + c] = acc;
-      }
-    }
-    __syncthreads();
-    for (int e = tid; e < nb * W; e += LU_THREADS) {
-      const int r = e / W, c = e % W;
-      A[(int64_t)(k0 + r) * N + k0 + nb + c] = U[r * US + c];
-    }
-    // 6. trailing update A22 -= L21 U12 on the matrix cores, 16x16 tiles
-    const int tr = (W + 15) / 16;
-    const int row = lane % 16, kq = lane / 16;
-    for (int t = wave; t < tr * tr; t += LU_THREADS / 64) {
-      const int r0 = (t / tr) * 16, c0 = (t % tr) * 16;
-      typename Mfma<T>::acc_t acc;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int rr = r0 + Mfma<T>::row(kq, i), cc = c0 + row;
-        acc[i] = (rr < W && cc < W) ? A[(int64_t)(k0 + nb + rr) * N + k0 + nb + cc] : T(0);
-      }
-#pragma unroll
-      for (int kk = 0; kk < NB; kk += 4) {
-        const int ar = r0 + row, bc = c0 + row, kx = kk + kq;
-        const T a = (ar < W && kx < nb) ? -Pn[(nb + ar) * PS + kx] : T(0);
-        const T b = (bc < W && kx < nb) ? U[kx * US + bc] : T(0);
-        acc = Mfma<T>::run(a, b, acc);
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int rr = r0 + Mfma<T>::row(kq, i), cc = c0 + row;
-        if (rr < W && cc < W) A[(int64_t)(k0 + nb + rr) * N + k0 + nb + cc] = acc[i];
-      }
-    }
-    __syncthreads();
-  }
-  if (tid == 0 && singular) status[st] = sing_code;
 }
 
 __global__ void zero_int_kernel(int* p) { *p = 0; }
@@ -957,93 +790,6 @@ hipError_t launch_small(int N, int64_t n, int64_t ld, const double* jac, const d
   return hipErrorInvalidValue;
 }
 
-// ---------------------------------------------------------------- solve
-// One wavefront per (listed) state, 4 states per 256-thread block; waves
-// without work stay in the block and only skip the memory operations, so
-// every barrier is reached by all four.
-// direct: x = A^-1 b, b from rhs [N][ld], x to xout [N][ld].
-// refine: d = A^-1 r with r from rbuf [N][n]; x += d in xs [N][n] (FP64) and
-//   the state converges at this sweep when ||d||_inf <= rtol ||x||_inf.
-template <typename T, bool REFINE>
-__global__ __launch_bounds__(256) void solve_kernel(int N, int64_t n, int64_t ld, const T* __restrict__ Aall,
-                                                    const int* __restrict__ pivall, const double* __restrict__ rhs,
-                                                    const double* __restrict__ rbuf, double* __restrict__ xs,
-                                                    double* __restrict__ xout, const int* __restrict__ list,
-                                                    const int* __restrict__ count, int* __restrict__ status,
-                                                    int sweep, double rtol, double* __restrict__ dprev) {
-  extern __shared__ char smem[];
-  const int lane = threadIdx.x % 64, wv = threadIdx.x / 64;
-  const int64_t slot = (int64_t)blockIdx.x * 4 + wv;
-  const int64_t lim = count ? *count : n;
-  bool active = slot < lim;
-  const int64_t st = active ? (list ? list[slot] : slot) : 0;
-  const int s0 = active ? status[st] : 0;
-  active = active && (REFINE ? s0 == ST_UNSET : (s0 != -3 && s0 != -1 && s0 != ST_SING32));
-  T* y = reinterpret_cast<T*>(smem) + (size_t)wv * N;
-  const T* A = Aall + (active ? slot : 0) * (int64_t)N * N;
-  const int* piv = pivall + (active ? slot : 0) * (int64_t)N;
-  if (active)
-    for (int i = lane; i < N; i += 64) y[i] = REFINE ? (T)rbuf[(int64_t)i * n + st] : (T)rhs[(int64_t)i * ld + st];
-  __syncthreads();
-  if (active && lane == 0)
-    for (int i = 0; i < N; ++i) {
-      const int p = piv[i];
-      if (p != i) { T t = y[i]; y[i] = y[p]; y[p] = t; }
-    }
-  __syncthreads();
-  for (int i = 1; i < N; ++i) {            // unit lower
-    T acc = T(0);
-    if (active)
-      for (int j = lane; j < i; j += 64) acc += A[(int64_t)i * N + j] * y[j];
-    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
-    if (active && lane == 0) y[i] -= acc;
-    __syncthreads();
-  }
-  for (int i = N - 1; i >= 0; --i) {       // upper
-    T acc = T(0);
-    if (active)
-      for (int j = i + 1 + lane; j < N; j += 64) acc += A[(int64_t)i * N + j] * y[j];
-    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
-    if (active && lane == 0) y[i] = (y[i] - acc) / A[(int64_t)i * N + i];
-    __syncthreads();
-  }
-  if (!active) return;
-  if (!REFINE) {
-    bool fin = true;
-    for (int i = lane; i < N; i += 64) {
-      xout[(int64_t)i * ld + st] = (double)y[i];
-      fin = fin && isfinite((double)y[i]);
-    }
-    fin = __all(fin);
-    if (lane == 0 && s0 == ST_UNSET) status[st] = fin ? 0 : -1;
-    return;
-  }
-  double dmax = 0.0, xmax = 0.0;
-  bool fin = true;
-  for (int i = lane; i < N; i += 64) {
-    const double d = (double)y[i];
-    const double xv = xs[(int64_t)i * n + st] + d;
-    xs[(int64_t)i * n + st] = xv;
-    dmax = fmax(dmax, fabs(d));
-    xmax = fmax(xmax, fabs(xv));
-    fin = fin && isfinite(xv);
-  }
-  for (int o = 32; o > 0; o >>= 1) {
-    dmax = fmax(dmax, __shfl_xor(dmax, o));
-    xmax = fmax(xmax, __shfl_xor(xmax, o));
-  }
-  fin = __all(fin);
-  if (lane == 0 && sweep > 0) {
-    // converged when the correction is below rtol of the solution, or when
-    // the contraction rho of the last two corrections (refinement converges
-    // linearly) predicts the remaining error rho / (1 - rho) |d| below it
-    const double dp = sweep >= 2 ? dprev[st] : 0.0;
-    const double rho = dp > 0.0 ? dmax / dp : 1.0;
-    if (fin && (dmax <= rtol * xmax || (rho < 0.5 && rho * dmax <= rtol * xmax * (1.0 - rho)))) status[st] = sweep;
-    dprev[st] = dmax;
-  }
-}
-
 // r = b - (I - h gamma J) x in FP64.  grid (ceil(n / 256), ceil(N / 8)): one
 // thread per (state, block of 8 rows), so that a few thousand states still
 // fill the device; each x_j load serves 8 multiply-adds and every load is
@@ -1163,8 +909,6 @@ WsLayout ws_layout(int N, int64_t n, int mode) {
   return L;
 }
 
-size_t lu_lds(int N, size_t elem) { return ((size_t)N * (NB + 1) + (size_t)NB * (N + 1) + LU_THREADS) * elem + LU_THREADS * sizeof(int); }
-
 template <typename T>
 hipError_t run_direct(int N, int64_t n, int64_t ld, const double* jac, const double* h, double gamma,
                       const double* rhs, double* x, T* A, int* piv, const int* list, const int* count, int* status,
@@ -1172,18 +916,13 @@ hipError_t run_direct(int N, int64_t n, int64_t ld, const double* jac, const dou
   if (factor) {
     dim3 fg((unsigned)((n + 15) / 16), (unsigned)(((int64_t)N * N + 63) / 64));
     hipLaunchKernelGGL(form_kernel<T>, fg, dim3(256), 0, st, N, n, ld, jac, h, gamma, A, list, count, status);
-    const size_t lds = lu_lds(N, sizeof(T));
-    hipError_t e = hipFuncSetAttribute((const void*)lu_kernel<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    const hipError_t e = launch_lu(N, n, A, piv, list, count, status, -1, st);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(lu_kernel<T>, dim3((unsigned)n), dim3(LU_THREADS), lds, st, N, n, A, piv, list, count, status, -1);
     if (save_status)
       hipLaunchKernelGGL(copy_status_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n,
                          (const int*)status, save_status);
   }
-  hipLaunchKernelGGL((solve_kernel<T, false>), dim3((unsigned)((n + 3) / 4)), dim3(256), 4 * N * sizeof(T), st, N, n, ld,
-                     (const T*)A, (const int*)piv, rhs, (const double*)nullptr, (double*)nullptr, x, list, count, status, 0,
-                     0.0, (double*)nullptr);
-  return hipGetLastError();
+  return launch_solve_direct<T>(N, n, ld, A, piv, rhs, x, list, count, status, st);
 }
 
 // Scratch for the no-allocation entry point: a file-scope device array, one
@@ -1298,7 +1037,7 @@ pyjac_status pyjac_newton_factor_solve(const pyjac_mech* m, int64_t n, int64_t l
   }
   const WsLayout L = ws_layout(N, n, mode);
   if (!workspace || workspace_bytes < L.total) return fail(PYJAC_E_WORKSPACE, "workspace smaller than pyjac_newton_workspace_bytes");
-  if (lu_lds(N, sizeof(double)) > 163840) return fail(PYJAC_E_UNSUPPORTED, "mechanism too large for the LU kernel");
+  if (N > kBlockedMax) return fail(PYJAC_E_UNSUPPORTED, "mechanism too large for the LU kernel");
   char* w = static_cast<char*>(workspace);
   int* status = reinterpret_cast<int*>(w + L.status);
   int* fbs = reinterpret_cast<int*>(w + L.fbstatus);
@@ -1336,22 +1075,17 @@ pyjac_status pyjac_newton_factor_solve(const pyjac_mech* m, int64_t n, int64_t l
       dim3 fg((unsigned)((n + 15) / 16), (unsigned)(((int64_t)N * N + 63) / 64));
       hipLaunchKernelGGL(form_kernel<float>, fg, dim3(256), 0, st, N, n, ld, jac, h, gamma, A32, (const int*)nullptr,
                          (const int*)nullptr, status);
-      const size_t lds = lu_lds(N, sizeof(float));
-      e = hipFuncSetAttribute((const void*)lu_kernel<float>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      e = launch_lu(N, n, A32, piv, nullptr, nullptr, status, ST_SING32, st);
       if (e != hipSuccess) return fail(PYJAC_E_DEVICE, hipGetErrorString(e));
-      hipLaunchKernelGGL(lu_kernel<float>, dim3((unsigned)n), dim3(LU_THREADS), lds, st, N, n, A32, piv,
-                         (const int*)nullptr, (const int*)nullptr, status, ST_SING32);
       hipLaunchKernelGGL(copy_status_kernel, dim3(g1), dim3(256), 0, st, n, (const int*)status, sing);
     }
-    const unsigned gs = (unsigned)((n + 3) / 4);
     for (int sweep = 0; sweep <= max_refine; ++sweep) {
       if (sweep > 0)
         hipLaunchKernelGGL(residual_kernel, dim3(g1, (unsigned)((N + kResRows - 1) / kResRows)), dim3(256), 0, st, N,
                            n, ld, jac, h, gamma, rhs, (const double*)xs,
                            rbuf, (const int*)status);
-      hipLaunchKernelGGL((solve_kernel<float, true>), dim3(gs), dim3(256), 4 * N * sizeof(float), st, N, n, ld,
-                         (const float*)A32, (const int*)piv, (const double*)nullptr, (const double*)rbuf, xs,
-                         (double*)nullptr, (const int*)nullptr, (const int*)nullptr, status, sweep, rtol, dprev);
+      e = launch_solve_refine(N, n, A32, piv, rbuf, xs, status, sweep, rtol, dprev, st);
+      if (e != hipSuccess) return fail(PYJAC_E_DEVICE, hipGetErrorString(e));
     }
     // FP64 re-solve of the states that did not converge (or whose FP32 factor was singular)
     hipLaunchKernelGGL(zero_int_kernel, dim3(1), dim3(1), 0, st, count);

@@ -1,0 +1,78 @@
+"""Newton solves over the system sizes at which the blocked path (N > 64)
+changes its kernels: panels of 32 columns (16 above 512 rows), one row per
+thread of 128-, 256-, 512- and 1,024-thread workgroups, and 2 to 10 rows per
+lane in the triangular solves.  The matrices are random with a zero leading
+block, so that every panel exchanges rows; bar 100 kappa u as for the LU of
+the other Newton tests (kappa stays far below 1/u32 here, so the mixed mode's
+refinement holds the same bar).
+"""
+import numpy as np
+import pytest
+
+U = 2.0 ** -53
+GAMMA = 0.5
+
+
+def isomer_mechanism(n):
+    """n species of the same composition and one reaction: a handle of that size."""
+    out = ["pyjac-mech 1", "elements 1", "  H 1.008", f"species {n}"]
+    for k in range(n):
+        out += [f"  S{k} 2.016 1000.0 1 H 2"] + ["    2.5 0.0 0.0 0.0 0.0 100.0 1.0"] * 2
+    out += ["reactions 1", "reaction elementary irrev", "reactants 1 S0 1", "products 1 S1 1",
+            "arrhenius 1.0 0.0 0.0", "end"]
+    return "\n".join(out) + "\n"
+
+
+def systems(N, n):
+    rng = np.random.default_rng(N)
+    A = rng.standard_normal((N, N, n))
+    z = N // 3
+    A[:z, :z, :] = 0.0
+    h = rng.uniform(0.5, 2.0, n)
+    J = (np.eye(N)[:, :, None] - A) / (h * GAMMA)
+    return J.reshape(N * N, n), h, rng.standard_normal((N, n))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("N", [65, 66, 95, 96, 97, 127, 128, 129, 160, 192, 193, 255, 256, 257, 320, 384, 385, 511,
+                               512, 513, 528, 607, 608])
+def test_blocked_sizes(N):
+    import torch
+    from oracle.newton_ref import newton_reference
+    from paper_1605_03262_amd import (Mechanism, NEWTON_FP64, NEWTON_KEEP_FACTOR, NEWTON_MIXED,
+                                      NEWTON_REUSE_FACTOR)
+    n = 3
+    J, h, b = systems(N, n + 2)
+    J[:, n], h[n] = 0.0, 2.0                            # state n: A = I but for an exactly zero row
+    J.reshape(N, N, n + 2)[N // 2, N // 2, n] = 1.0
+    J[7, n + 1] = np.inf                                # state n + 1: not finite
+    xr, kappa = newton_reference(J[:, :n], h[:n], GAMMA, b[:, :n])
+    M = Mechanism(text=isomer_mechanism(N))
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    dJ, dh, db, db2 = d(J), d(h), d(b), d(2.0 * b)
+    bar = 100 * kappa * U
+    for mode in (NEWTON_FP64, NEWTON_MIXED):
+        ws = torch.empty((M.newton_workspace_bytes(n + 2, mode | NEWTON_KEEP_FACTOR),), dtype=torch.uint8,
+                         device="cuda")
+        x, info = M.newton_solve(dJ, dh, db, GAMMA, mode=mode | NEWTON_KEEP_FACTOR, workspace=ws)
+        x2, info2 = M.newton_solve(dJ, dh, db2, GAMMA, mode=mode | NEWTON_REUSE_FACTOR, workspace=ws)
+        x, x2, info, info2 = x.cpu().numpy(), x2.cpu().numpy(), info.cpu().numpy(), info2.cpu().numpy()
+        assert info[n] == -1 and info[n + 1] == -3 and np.array_equal(info2[n:], info[n:]), (info, info2)
+        assert np.all(info[:n] == 0) if mode == NEWTON_FP64 else np.all((info[:n] >= 1) | (info[:n] == -2)), info
+        err = np.max(np.abs(x[:, :n] - xr), axis=0) / np.max(np.abs(xr), axis=0)
+        assert np.all(err <= bar), (mode, err / bar)
+        if mode == NEWTON_FP64:                         # twice the right-hand side: exactly twice the solution
+            assert np.array_equal(x2[:, :n], 2.0 * x[:, :n])
+
+
+@pytest.mark.gpu
+def test_largest_size():
+    import torch
+    from paper_1605_03262_amd import Mechanism, PyjacError
+    N, n = 609, 1
+    J, h, b = systems(N, n)
+    M = Mechanism(text=isomer_mechanism(N))
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    with pytest.raises(PyjacError, match="too large"):
+        M.newton_solve(d(J), d(h), d(b), GAMMA, mode=0)
+    torch.cuda.synchronize()
