@@ -55,12 +55,13 @@ struct pyjac_mech {
   int device = 0;
   size_t max_lds = 65536;
   pyjac::Variant jac_var, rates_var, conc_var;
-  // per launch shape: species-list chunk bounds, built when the shape is chosen
+  // per launch shape: gather lists, built when the shape is chosen
   struct VarDev {
     int ts = 0, nt = 0;
     bool jac = false;
     void* mem = nullptr;
-    const int* chunk = nullptr;
+    const int* meta = nullptr;
+    const pyjac::GatherBlk* blk = nullptr;
   };
   std::vector<VarDev> vars;
 };
@@ -121,7 +122,6 @@ pyjac_status upload(pyjac_mech* m) {
   append(blob, P.vcol.empty() ? std::vector<double>{0.0} : P.vcol, o);
   append(blob, P.rx, o);
   append(blob, P.eff_sp, o); append(blob, P.eff_am1, o); append(blob, P.plog, o); append(blob, P.cheb, o);
-  append(blob, P.spg_ent, o);
   append(blob, P.col_start, o); append(blob, P.colrec, o); append(blob, P.col_order, o);
   append(blob, P.col_flags, o);
   append(blob, P.col_item, o); append(blob, P.col_join, o);
@@ -140,14 +140,14 @@ pyjac_status upload(pyjac_mech* m) {
   d.rx = D((const RxnRec*)0);
   d.eff_sp = D((const int*)0); d.eff_am1 = D((const double*)0); d.plog = D((const double*)0);
   d.cheb = D((const double*)0);
-  d.spg_ent = D((const int*)0);
   d.col_start = D((const int*)0); d.colrec = D((const ColRec*)0); d.col_order = D((const int*)0);
   d.col_flags = D((const uint32_t*)0);
   d.col_item = D((const ColItem*)0); d.col_join = D((const ColJoin*)0);
   d.n_col_item = (int)P.col_item.size(); d.n_col_join = (int)P.col_join.size();
   d.cv_col_start = D((const int*)0); d.cv_colrec = D((const ColRec*)0); d.cv_col_order = D((const int*)0);
   d.cv_colptr = D((const int*)0);
-  d.spg_chunk = nullptr;
+  d.spg_meta = nullptr;
+  d.spg_blk = nullptr;
   return PYJAC_OK;
 }
 
@@ -158,7 +158,9 @@ pyjac_status ensure_var(pyjac_mech* m, Variant v, bool jac) {
   vd.ts = v.ts; vd.nt = v.nt; vd.jac = jac;
   std::vector<char> blob;
   std::vector<size_t> o;
-  append(blob, species_chunk_bounds(m->host, v.nt / v.ts), o);
+  const GatherLists G = gather_lists(m->host, v.nt / v.ts);
+  append(blob, G.meta, o);
+  append(blob, G.blk, o);
   int prev = 0;
   hipGetDevice(&prev);
   hipSetDevice(m->device);
@@ -168,7 +170,8 @@ pyjac_status ensure_var(pyjac_mech* m, Variant v, bool jac) {
   if (e1 != hipSuccess) return fail(PYJAC_E_NOMEM, "hipMalloc of launch tables failed");
   if (e2 != hipSuccess) { hipFree(vd.mem); return fail(PYJAC_E_DEVICE, "copy of launch tables failed"); }
   char* b = static_cast<char*>(vd.mem);
-  vd.chunk = reinterpret_cast<const int*>(b + o[0]);
+  vd.meta = reinterpret_cast<const int*>(b + o[0]);
+  vd.blk = reinterpret_cast<const GatherBlk*>(b + o[1]);
   m->vars.push_back(vd);
   return PYJAC_OK;
 }
@@ -176,7 +179,10 @@ pyjac_status ensure_var(pyjac_mech* m, Variant v, bool jac) {
 MechDev launch_view(const pyjac_mech* m, Variant v, bool jac) {
   MechDev md = m->dev;
   for (auto& e : m->vars)
-    if (e.ts == v.ts && e.nt == v.nt && e.jac == jac) md.spg_chunk = e.chunk;
+    if (e.ts == v.ts && e.nt == v.nt && e.jac == jac) {
+      md.spg_meta = e.meta;
+      md.spg_blk = e.blk;
+    }
   return md;
 }
 

@@ -160,7 +160,7 @@ __global__ void cs_jacobian_kernel(MechDev md, int64_t n, int64_t ld, const doub
         cd sB = mk(R.dnu_lnpr);
         for (int q = 0; q < kMaxNet; ++q) {
           const int v = R.net[q];
-          if (v == -1) break;
+          if (!(v >> 16)) break;               // unused entries have nu = 0
           sB = sB + (double)(v >> 16) * Bk[v & 0xFFFF];
         }
         kr = kf * cexp_(-sB);                          // k_r = k_f / K_c
@@ -222,7 +222,7 @@ __global__ void cs_jacobian_kernel(MechDev md, int64_t n, int64_t ld, const doub
       const cd q = c * (Rf - Rr);
       for (int u = 0; u < kMaxNet; ++u) {
         const int v = R.net[u];
-        if (v == -1) break;
+        if (!(v >> 16)) break;               // unused entries have nu = 0
         const int k = v & 0xFFFF;
         wd[k] = wd[k] + (double)(v >> 16) * q;
       }

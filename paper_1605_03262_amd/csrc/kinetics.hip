@@ -8,10 +8,19 @@
 // layout).  All per-state temporaries of the tile stay in LDS:
 //   persistent : X[N+1] (concentrations, X[N] = 1), KF[NR] = c k_f,
 //                KR[NR] = c k_r, G[NG] = (dc/dE) R, per-state scalars
-//   alias      : phase A  Bk[N], dBk[N], per-species c_p terms [2][N]
-//                phase B  Bk[N], dBk[N], chunk[2][4][G] of per-reaction results
-//                         (two buffers used in turn)
-//                phase C+ WA[N], WB[N], JT[N], H[N], per-species sum terms [2][N]
+//   alias      : phase A  (B_k, dB_k)[N], per-species c_p terms [2][N]
+//                phase B  (B_k, dB_k)[N], chunk[2][4][G + 1] of per-reaction
+//                         results (two buffers used in turn; row G is zero)
+//                phase C+ (A_k, B_k)[N], H[N], per-species sum terms [2][N]
+//
+// What bounds these kernels: latency and instruction issue (four wavefronts
+// per SIMD keep the vector units about half busy), not HBM.  Measured on 53
+// species and 100,000 states (Jacobian, 4 x 256) and 111 species and 20,001
+// states (4 x 256): 1.71 and 1.38 ms with the species gathers reading their
+// lists entry by entry from L2, 1.53 and 1.18 ms with packed lists fetched
+// ahead and branch-free reads of the equilibrium terms, 1.30 and 1.13 ms with
+// exponentials and logarithms that keep their constants out of vector
+// registers (163 -> 128 registers, a fourth wavefront per SIMD).
 // Every per-state sum over species is formed by one thread in species order
 // and no atomics are used, so a state's results depend neither on its
 // neighbours nor on the launch shape (TS, NT).
@@ -46,18 +55,19 @@ enum { SC_T = 0, SC_IT, SC_LT, SC_P, SC_LP, SC_L10P, SC_RHO, SC_W, SC_M, SC_CP, 
 enum { SC_IM = SC_RHO, SC_DEN = SC_CP, SC_SUW = SC_DCP, SC_SUU = SC_SHW };
 
 // Register budget of the tile kernels, as wavefronts per SIMD: 4 (128
-// registers) for 512- and 1024-thread workgroups; 3 (168 registers, no
-// spills at 53 species) for 256-thread ones, whose LDS lets three
-// workgroups share a CU.
-constexpr int tile_waves_per_eu(int nt) { return nt == 256 ? 3 : (nt <= 512 ? 4 : 1); }
+// registers), also for 256-thread workgroups with one species per thread (53
+// species, four workgroups per CU: 1.34 ms against 1.44 at three); 3 (168
+// registers) for 256-thread workgroups with more, which LDS limits to two per
+// CU anyway (111 species: 1.13 ms against 1.21 at four).
+constexpr int tile_waves_per_eu(int nt, int kpt) { return nt == 256 ? (kpt <= 1 ? 4 : 3) : (nt <= 512 ? 4 : 1); }
 
 // Phase B keeps its per-reaction results in two buffers used in turn (one
 // barrier per reaction chunk instead of two) when the second buffer costs no
 // workgroup per CU: the workgroups a CU holds are the fewer of what its
 // register budget (4 SIMDs) and its 160 KiB of LDS allow.
-__host__ __device__ inline bool two_chunk_buffers(int rows1, int rows2, int TS, int NT) {
+__host__ __device__ inline bool two_chunk_buffers(int N, int rows1, int rows2, int TS, int NT) {
   const int waves = NT / 64;
-  const int by_regs = (4 * (NT == 256 ? 3 : 4)) / waves;
+  const int by_regs = (4 * (NT == 256 && N > NT / TS ? 3 : 4)) / waves;
   const int lds1 = (160 * 1024) / (rows1 * TS * 8), lds2 = (160 * 1024) / (rows2 * TS * 8);
   const int wg1 = by_regs < lds1 ? by_regs : lds1, wg2 = by_regs < lds2 ? by_regs : lds2;
   return wg2 >= wg1;
@@ -67,9 +77,10 @@ __host__ __device__ inline bool two_chunk_buffers(int rows1, int rows2, int TS, 
 struct TileLayout {
   int X, KF, KR, G, SC, alias;
   int Bk, dBk, chunk, redA;      // phases A/B (alias)
-  int WA, WB, JT, H, redC;       // phases C/D (alias)
+  int WA, H, redC;               // phases C/D (alias)
   int rows;                      // total rows
   int nbuf;                      // phase-B chunk buffers (1 or 2)
+  bool early;                    // see below
   __host__ __device__ TileLayout(int N, int NR, int NG, int TS, int NT, bool jac) {
     const int Gr = NT / TS;
     X = 0;
@@ -83,19 +94,21 @@ struct TileLayout {
     redA = dBk + (jac ? N : 0);             // per-species terms summed in species order
     chunk = redA;                           // phase B reuses the phase-A reduction rows
     int endA = redA + (jac ? 2 : 1) * N;
-    WA = alias;                             // WA and WB interleaved: [k][s][2], k = 0..N (row N: slack)
-    WB = WA;
-    JT = WA + (jac ? 2 * (N + 1) : 0);
-    H = JT + (jac ? N : 0);                 // k = 0..N (row N: slack)
+    WA = alias;                             // (A_k, B_k) pairs: [k][s][2], k = 0..N (row N: slack)
+    H = WA + (jac ? 2 * (N + 1) : 0);       // k = 0..N (row N: slack)
     redC = H + (jac ? N + 1 : 0);
     int endC = redC + (jac ? 2 : 1) * N;
     auto total = [&](int nb) {
-      const int endB = chunk + nb * (jac ? 4 : 1) * Gr;
+      const int endB = chunk + nb * (jac ? 4 : 1) * (Gr + 1);
       const int e = endB > endA ? endB : endA;
       return e > endC ? e : endC;
     };
-    nbuf = two_chunk_buffers(total(1), total(2), TS, NT) ? 2 : 1;
+    nbuf = two_chunk_buffers(N, total(1), total(2), TS, NT) ? 2 : 1;
     rows = total(nbuf);
+    // the phase-A sum terms fit the second buffer: they are summed while the
+    // first reaction chunk is evaluated, without a barrier of their own
+    early = nbuf == 2 && (jac ? 2 : 1) * N <= (jac ? 4 : 1) * Gr;
+    if (early) redA = chunk + (jac ? 4 : 1) * (Gr + 1);
   }
 };
 
@@ -108,6 +121,69 @@ __device__ inline const double* nasa_coeffs(const MechDev& md, int k, double T) 
   return md.nasa + (size_t)k * 14 + (T <= md.tmid[k] ? 0 : 7);
 }
 
+// exp of a finite argument (a NaN stays one; overflow and underflow end in inf
+// and 0): n = rint(x / ln 2), r = x - n ln 2 in two fused steps, and a
+// polynomial of degree 11 on |r| <= ln 2 / 2 (the series' second-order
+// remainder interpolated at Chebyshev nodes, 1.6e-17 relative), then 2^n.
+// Below 1 ulp, as the library's exp, in 18 instructions against about 35: the
+// polynomial's constants stay in scalar registers as the addend of a
+// three-address fused multiply-add, where the compiler keeps each in a vector
+// register pair and copies it before an accumulating one.
+__device__ __forceinline__ double fma_sc(double a, double b, double c) {
+  double d;
+  __asm__("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "s"(c));
+  return d;
+}
+__device__ __forceinline__ double exp_rate(double x) {
+  const double n = rint(x * 0x1.71547652b82fep+0);
+  double r = fma(n, -0x1.62e42fefa39efp-1, x);
+  r = fma(n, -0x1.abc9e3b39803fp-56, r);
+  double q = fma_sc(r, 0x1.af38a9b0ec855p-26, 0x1.289185613a3d6p-22);
+  q = fma_sc(r, q, 0x1.71de0dae63bb3p-19);
+  q = fma_sc(r, q, 0x1.a019b90d2ae7ap-16);
+  q = fma_sc(r, q, 0x1.a01a01a7c41d5p-13);
+  q = fma_sc(r, q, 0x1.6c16c1788bd90p-10);
+  q = fma_sc(r, q, 0x1.11111111109b3p-7);
+  q = fma_sc(r, q, 0x1.5555555553d63p-5);
+  q = fma_sc(r, q, 0x1.5555555555556p-3);
+  q = fma_sc(r, q, 0x1.0000000000001p-1);
+  q = fma(r, q, 1.0);
+  return ldexp(fma(r, q, 1.0), (int)n);
+}
+// exp of any argument
+__device__ __forceinline__ double exp_any(double x) {
+  const double y = exp_rate(x);
+  return fabs(x) < INFINITY ? y : (x > 0.0 ? x : (x < 0.0 ? 0.0 : x));
+}
+// Natural logarithm, scalar constants as in exp_rate: x = 2^e m with m in
+// [sqrt(1/2), sqrt(2)), f = m - 1, s = f / (2 + f), and
+// log(1 + f) = 2 atanh(s) = f - s (f - t), t = s^2 P(s^2) with P the tail of
+// the atanh series interpolated at Chebyshev nodes (below 1e-17 relative).
+__device__ __forceinline__ double log_any(double x) {
+  int e;
+  double m = frexp(x, &e);
+  const bool lo = m < 0x1.6a09e667f3bcdp-1;
+  m = lo ? m + m : m;
+  const double k = (double)(lo ? e - 1 : e);
+  const double f = m - 1.0, d = m + 1.0;
+  double r = __builtin_amdgcn_rcp(d);
+  r = fma(r, fma(-d, r, 1.0), r);
+  r = fma(r, fma(-d, r, 1.0), r);
+  double s = f * r;
+  s = fma(r, fma(-d, s, f), s);
+  const double z = s * s;
+  double q = fma_sc(z, 0x1.2b5f68a50d903p-3, 0x1.39fdcceb4bb45p-3);
+  q = fma_sc(z, q, 0x1.7462b91b8df65p-3);
+  q = fma_sc(z, q, 0x1.c71c62d5e53e0p-3);
+  q = fma_sc(z, q, 0x1.2492492dfd86cp-2);
+  q = fma_sc(z, q, 0x1.9999999995273p-2);
+  q = fma_sc(z, q, 0x1.5555555555558p-1);
+  double y = fma(k, 0x1.abc9e3b39803fp-56, -(s * fma(-z, q, f)));
+  y = fma(k, 0x1.62e42fefa39efp-1, y + f);
+  y = x > 0.0 ? y : (x == 0.0 ? -INFINITY : NAN);
+  return x < INFINITY ? y : x;
+}
+
 // Per-reaction evaluation for one state.  Xs points at X[0][s] (stride TS);
 // R is the reaction's packed record, fetched by the caller before any branch.
 // CV selects the concentration-based, constant-volume form: temperature
@@ -118,8 +194,7 @@ __device__ inline const double* nasa_coeffs(const MechDev& md, int k, double T) 
 // dependence) is returned in o.a; iM = 1 / sum [X] is then used.
 template <int TS, bool JAC, bool CV = false>
 __device__ inline void eval_reaction(const MechDev& md, const RxnRec& R, const RxnRec* __restrict__ Rg,
-                                     const double* Xs,
-                                     const double* Bks, const double* dBks, double T, double iT,
+                                     const double* Xs, const double* Bks, double T, double iT,
                                      double lT, double lp, double l10p, double rho, double irho,
                                      double W, double M, RxnResult& o, double iM = 0.0) {
   const int info = R.info;
@@ -130,7 +205,7 @@ __device__ inline void eval_reaction(const MechDev& md, const RxnRec& R, const R
   // ---- forward rate coefficient and D_f = T dln k_f/dT (Sec. 2.3, 2.3.4; Sec. 3.1)
   double kf, Df, Dp = 0.0;            // Dp = d ln k_f / d ln p (CV form only)
   if (kind <= K_CHEMACT) {
-    kf = ar[0] * exp(ar[1] * lT - ar[2] * iT);
+    kf = ar[0] * exp_rate(ar[1] * lT - ar[2] * iT);
     Df = ar[1] + ar[2] * iT;
   } else if (kind == K_PLOG) {
     const int p0 = R.aux0, p1 = R.aux1;
@@ -158,7 +233,7 @@ __device__ inline void eval_reaction(const MechDev& md, const RxnRec& R, const R
       lk1 = lk1 + (lk2 - lk1) * frac;
       D1 = D1 + (D2 - D1) * frac;
     }
-    kf = exp(lk1);
+    kf = exp_rate(lk1);
     Df = D1;
   } else {   // Chebyshev
     const double* cb = md.cheb + R.aux0;
@@ -194,7 +269,7 @@ __device__ inline void eval_reaction(const MechDev& md, const RxnRec& R, const R
       Um2 = Um1;
       Um1 = Un;
     }
-    kf = exp(kLn10 * val);
+    kf = exp_rate(kLn10 * val);
     Df = -kLn10 * dval * cb[2] * iT;
     if (CV) Dp = pval * cb[4];         // d log10 k / d log10 p
   }
@@ -202,18 +277,36 @@ __device__ inline void eval_reaction(const MechDev& md, const RxnRec& R, const R
   double kr = 0.0, Dr = 0.0;
   if (rev == R_KC) {
     double sB = 0.0, sdB = 0.0;
+    // the unused entries of the list have nu = 0 and a valid species, so the
+    // reads need no condition and are in flight together
+    auto net = [&](int q0, int q1) {
+      double B[kMaxNet], dB[kMaxNet];
 #pragma unroll
-    for (int q = 0; q < kMaxNet; ++q) {
-      int v = R.net[q];
-      if (v == -1) break;
-      int k = v & 0xFFFF, nu = v >> 16;
-      sB += nu * Bks[k * TS];
-      if (JAC) sdB += nu * dBks[k * TS];
-    }
-    kr = kf * exp(-sB - R.dnu_lnpr);
+      for (int q = 0; q < kMaxNet; ++q)
+        if (q >= q0 && q < q1) {
+          const int k = R.net[q] & 0xFFFF;
+          if (JAC) {
+            const double2 b2 = reinterpret_cast<const double2*>(Bks)[k * TS];
+            B[q] = b2.x;
+            dB[q] = b2.y;
+          } else {
+            B[q] = Bks[k * TS];
+          }
+        }
+#pragma unroll
+      for (int q = 0; q < kMaxNet; ++q)
+        if (q >= q0 && q < q1) {
+          const double nu = (double)(R.net[q] >> 16);
+          sB += nu * B[q];
+          if (JAC) sdB += nu * dB[q];
+        }
+    };
+    net(0, 4);
+    if (R.net[4] >> 16) net(4, kMaxNet);
+    kr = kf * exp_rate(-sB - R.dnu_lnpr);
     Dr = Df - T * sdB;                 // K_c depends on T only: d ln k_r / d ln p = Dp
   } else if (rev == R_EXPLICIT) {
-    kr = arg[6] * exp(arg[7] * lT - arg[8] * iT);
+    kr = arg[6] * exp_rate(arg[7] * lT - arg[8] * iT);
     Dr = arg[7] + arg[8] * iT;
   }
   // ---- mass-action products over the molecule lists (absent molecules read X[N] = 1)
@@ -247,28 +340,28 @@ __device__ inline void eval_reaction(const MechDev& md, const RxnRec& R, const R
       psi = 1.0;
       dcdT = CV ? 0.0 : -E * iT;       // constant p: [X] ~ 1/T; constant volume: fixed
     } else {
-      const double ratio = arg[3] * exp(arg[4] * lT - arg[5] * iT);   // k0 / kinf
+      const double ratio = arg[3] * exp_rate(arg[4] * lT - arg[5] * iT);   // k0 / kinf
       const double Pr = ratio * E;
       double F = 1.0, Lam = 0.0, dlnFdT = 0.0;
       const double* fp = Rg->fpar;
       if (blend == B_TROE) {
         const double a = fp[0], r3 = Rg->frcp[0], r1 = Rg->frcp[1];
-        const double e3 = exp(-T * r3), e1 = exp(-T * r1);
+        const double e3 = exp_any(-T * r3), e1 = exp_any(-T * r1);
         double Fc = (1.0 - a) * e3 + a * e1;
         double dFc = -(1.0 - a) * r3 * e3 - a * r1 * e1;
         if (info & F_TROE_T2) {
-          double e2 = exp(-fp[3] * iT);
+          double e2 = exp_any(-fp[3] * iT);
           Fc += e2;
           dFc += fp[3] * iT * iT * e2;
         }
-        const double lnFc = log(Fc);
+        const double lnFc = log_any(Fc);
         if (Pr > 0.0) {
-          const double lFc = lnFc * kInvLn10, lPr = log(Pr) * kInvLn10;
+          const double lFc = lnFc * kInvLn10, lPr = log_any(Pr) * kInvLn10;
           const double At = lPr - 0.67 * lFc - 0.4;
           const double Bt = 0.806 - 1.1762 * lFc - 0.14 * lPr;
           const double iBt = 1.0 / Bt, iFc = 1.0 / Fc;
           const double r = At * iBt, den = 1.0 + r * r, iden = 1.0 / den;
-          F = exp(lnFc * iden);
+          F = exp_any(lnFc * iden);
           const double iden2B3 = iden * iden * iBt * iBt * iBt;          // 1 / (den^2 B^3)
           Lam = -lnFc * 2.0 * At * (Bt + 0.14 * At) * kInvLn10 * iden2B3;
           const double dAB = (-0.67 * Bt + 1.1762 * At) * kInvLn10 * iFc;   // (dA/dFc B - A dB/dFc)
@@ -278,19 +371,19 @@ __device__ inline void eval_reaction(const MechDev& md, const RxnRec& R, const R
           // no collider present: the limit P_r -> 0+, where A/B -> -1/0.14
           // and the P_r-derivative term of ln F vanishes
           constexpr double den0 = 1.0 + 1.0 / (0.14 * 0.14);
-          F = exp(lnFc / den0);
+          F = exp_any(lnFc / den0);
           dlnFdT = dFc / (Fc * den0);
         }
       } else if (blend == B_SRI) {
         const double rc = Rg->frcp[0];
-        const double ea = exp(-fp[1] * iT), ec = exp(-T * rc);
+        const double ea = exp_any(-fp[1] * iT), ec = exp_any(-T * rc);
         const double base = fp[0] * ea + ec;
         const double dbase = fp[0] * fp[1] * iT * iT * ea - ec * rc;
         // P_r <= 0 (no collider present) takes the limit P_r -> 0+: X -> 0
-        const double lPr = Pr > 0.0 ? log(Pr) * kInvLn10 : 0.0;
+        const double lPr = Pr > 0.0 ? log_any(Pr) * kInvLn10 : 0.0;
         const double Xs_ = Pr > 0.0 ? 1.0 / (1.0 + lPr * lPr) : 0.0;
-        const double lnb = log(base);
-        F = fp[3] * exp(fp[4] * lT + Xs_ * lnb);
+        const double lnb = log_any(base);
+        F = fp[3] * exp_any(fp[4] * lT + Xs_ * lnb);
         Lam = -lnb * Xs_ * Xs_ * 2.0 * lPr * kInvLn10;
         dlnFdT = fp[4] * iT + Xs_ * dbase / base;
       }
@@ -375,6 +468,25 @@ __device__ inline unsigned xcd_tile() {
   return x * q + (x < r ? x : r) + i;
 }
 
+// LDS address of row `half HI of w` of an array of TS doubles per row: one
+// 16-bit multiply-add on the packed field
+template <int TS, int HI>
+__device__ __forceinline__ unsigned row_addr(unsigned w, unsigned base) {
+  unsigned a;
+  if constexpr (HI) __asm__("v_mad_u32_u16 %0, %1, %2, %3 op_sel:[1,0,0,0]" : "=v"(a) : "v"(w), "s"(TS * 8), "v"(base));
+  else __asm__("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(a) : "v"(w), "s"(TS * 8), "v"(base));
+  return a;
+}
+typedef const __attribute__((address_space(3))) double* lds_cptr;
+__device__ __forceinline__ unsigned lds_addr(const double* p) { return (unsigned)(uintptr_t)(lds_cptr)p; }
+__device__ __forceinline__ double lds_read(unsigned a) { return *(lds_cptr)(uintptr_t)a; }
+// One term of a column stream (see ColRec).
+template <int TS>
+__device__ __forceinline__ double col_term(const ColRec& r, unsigned xb) {
+  return r.coef * lds_read(row_addr<TS, 0>(r.src, xb)) * lds_read(row_addr<TS, 0>(r.x, xb)) *
+         lds_read(row_addr<TS, 1>(r.x, xb));
+}
+
 // SPLIT selects the form of the Jacobian column streams: every row streamed
 // (false) or only the rows with terms, the others written by a dense pass (true).
 // The body of one tile (states tile*TS .. tile*TS + TS - 1 of the batch).
@@ -395,64 +507,124 @@ __device__ __forceinline__ void tile_body(const MechDev& md, unsigned tile, int6
   const TileLayout L(N, NR, NG, TS, NT, JAC);
   double* X = lds + (size_t)L.X * TS + s;
   double* SC = lds + (size_t)L.SC * TS + s;
-  double* Bk = lds + (size_t)L.Bk * TS + s;
-  double* dBk = lds + (size_t)L.dBk * TS + s;
+  // B_k and dB_k/dT, interleaved in Jacobian mode: [k][s][2]
+  double* Bk = lds + (size_t)L.Bk * TS + (JAC ? 2 : 1) * s;
   double* red = lds + (size_t)L.redA * TS + s;
-
   // ---- phase A1: mass fractions, Y_N, mean molecular weight, density (Sec. 2.1)
-  for (int k = g; k < N - 1; k += Gr) X[k * TS] = phi[(int64_t)(k + 1) * ld + sl];
-  __syncthreads();
-  if (g == 0) {
-    // Y_N = 1 - sum Y_k with Neumaier compensation: the difference can be
-    // tiny when the last species is scarce, so the sum is kept to ~1 ulp.
-    double sY = 0.0, cY = 0.0, sYW = 0.0;
-    for (int k = 0; k < N - 1; ++k) {
-      const double y = X[k * TS];
-      const double t = sY + y;
-      cY += (fabs(sY) >= fabs(y)) ? (sY - t) + y : (y - t) + sY;
-      sY = t;
-      sYW += y * md.invW[k];
+  const double Ts = phi[sl], ps = pin[sl];
+  {
+    double* red1 = lds + (size_t)L.chunk * TS + s;      // Y_k / W_k
+    for (int k = g; k < N - 1; k += Gr) {
+      const double y = phi[(int64_t)(k + 1) * ld + sl];
+      X[k * TS] = y;
+      red1[k * TS] = y * md.invW[k];
     }
-    const double YN = 1.0 - (sY + cY);
-    X[(N - 1) * TS] = YN;
-    X[N * TS] = 1.0;
-    sYW += YN * md.invW[N - 1];
-    const double T = phi[sl], p = pin[sl];
-    const double W = 1.0 / sYW;
-    SC[SC_T * TS] = T;
-    SC[SC_IT * TS] = 1.0 / T;
-    SC[SC_LT * TS] = log(T);
-    SC[SC_P * TS] = p;
-    const double lp = log(p);
-    SC[SC_LP * TS] = lp;
-    SC[SC_L10P * TS] = lp * kInvLn10;
-    SC[SC_W * TS] = W;
-    SC[SC_RHO * TS] = p * W / (kR * T);
-    SC[SC_IRHO * TS] = kR * T / (p * W);
-    SC[SC_M * TS] = p / (kR * T);
+    __syncthreads();
+    if (g == 0) {
+      // Y_N = 1 - sum Y_k with compensated summation (the rounding error of
+      // every addition is kept): the difference can be tiny when the last
+      // species is scarce, so the sum is kept to ~1 ulp.  Four interleaved
+      // partial sums in a fixed order (independent of the launch shape).
+      double sy[4] = {0.0, 0.0, 0.0, 0.0}, cy[4] = {0.0, 0.0, 0.0, 0.0}, sw[4] = {0.0, 0.0, 0.0, 0.0};
+      auto add = [](double& su, double& cu, double y) {
+        const double t = su + y, bb = t - su;
+        cu += (su - (t - bb)) + (y - bb);
+        su = t;
+      };
+      int k = 0;
+#pragma unroll 2
+      for (; k + 4 <= N - 1; k += 4) {
+        double y[4], w[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          y[u] = X[(k + u) * TS];
+          w[u] = red1[(k + u) * TS];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          add(sy[u], cy[u], y[u]);
+          sw[u] += w[u];
+        }
+      }
+      for (int u = 0; k < N - 1; ++k, ++u) {
+        const double y = X[k * TS], w = red1[k * TS];
+#pragma unroll
+        for (int v = 0; v < 3; ++v)
+          if (u == v) {
+            add(sy[v], cy[v], y);
+            sw[v] += w;
+          }
+      }
+#pragma unroll
+      for (int u = 1; u < 4; ++u) {
+        add(sy[0], cy[0], sy[u]);
+        cy[0] += cy[u];
+      }
+      const double YN = 1.0 - (sy[0] + cy[0]);
+      X[(N - 1) * TS] = YN;
+      X[N * TS] = 1.0;
+      const double W = 1.0 / (((sw[0] + sw[1]) + (sw[2] + sw[3])) + YN * md.invW[N - 1]);
+      const double M = ps / (kR * Ts);
+      SC[SC_M * TS] = M;
+      SC[SC_W * TS] = W;
+      SC[SC_RHO * TS] = W * M;
+      SC[SC_IRHO * TS] = 1.0 / (W * M);
+    }
+    if (g == Gr - 1) {
+      const double lp = log(ps);
+      SC[SC_T * TS] = Ts;
+      SC[SC_IT * TS] = 1.0 / Ts;
+      SC[SC_LT * TS] = log(Ts);
+      SC[SC_P * TS] = ps;
+      SC[SC_LP * TS] = lp;
+      SC[SC_L10P * TS] = lp * kInvLn10;
+    }
   }
-  __syncthreads();
-
   // ---- phase A2: concentrations and NASA-7 thermo (Sec. 2.2), B_k of Sec. 2.3.1
   // (the per-state scalars are read from LDS where they are used, here and in
-  // every reaction chunk, rather than held in registers across phase B)
+  // every reaction chunk, rather than held in registers across phase B; the
+  // first species' coefficients are fetched before the barrier)
+  double na[7];
+  {
+    const double* a = nasa_coeffs(md, min(g, N - 1), Ts);
+#pragma unroll
+    for (int u = 0; u < 7; ++u) na[u] = a[u];
+  }
+  __syncthreads();
   for (int k = g; k < N; k += Gr) {
-    const double T = SC[SC_T * TS], iT = SC[SC_IT * TS], lT = SC[SC_LT * TS];
+    const double T = Ts, iT = SC[SC_IT * TS], lT = SC[SC_LT * TS];
     const double rho = SC[SC_RHO * TS];
     const double y = X[k * TS];
     X[k * TS] = rho * y * md.invW[k];
-    const double* a = nasa_coeffs(md, k, T);
+    double a[7];
+    if (k == g) {
+#pragma unroll
+      for (int u = 0; u < 7; ++u) a[u] = na[u];
+    } else {
+      const double* ap = nasa_coeffs(md, k, T);
+#pragma unroll
+      for (int u = 0; u < 7; ++u) a[u] = ap[u];
+    }
     const double cpR = a[0] + T * (a[1] + T * (a[2] + T * (a[3] + a[4] * T)));
     const double rW = kR * md.invW[k];
     red[k * TS] = y * cpR * rW;
     if (JAC) red[(N + k) * TS] = y * rW * (a[1] + T * (2.0 * a[2] + T * (3.0 * a[3] + 4.0 * a[4] * T)));
-    Bk[k * TS] = a[6] - a[0] + (a[0] - 1.0) * lT +
-                 T * (a[1] * 0.5 + T * (a[2] * (1.0 / 6.0) + T * (a[3] * (1.0 / 12.0) + a[4] * 0.05 * T))) -
-                 a[5] * iT;
-    if (JAC)
-      dBk[k * TS] = (a[0] - 1.0 + a[5] * iT) * iT + a[1] * 0.5 +
-                    T * (a[2] * (1.0 / 3.0) + T * (a[3] * 0.25 + a[4] * 0.2 * T));
+    const double B = a[6] - a[0] + (a[0] - 1.0) * lT +
+                     T * (a[1] * 0.5 + T * (a[2] * (1.0 / 6.0) + T * (a[3] * (1.0 / 12.0) + a[4] * 0.05 * T))) -
+                     a[5] * iT;
+    if (JAC) {
+      const double dB = (a[0] - 1.0 + a[5] * iT) * iT + a[1] * 0.5 +
+                        T * (a[2] * (1.0 / 3.0) + T * (a[3] * 0.25 + a[4] * 0.2 * T));
+      reinterpret_cast<double2*>(Bk)[k * TS] = make_double2(B, dB);
+    } else {
+      Bk[k * TS] = B;
+    }
   }
+  // chunk results [row][s]: q, or in Jacobian mode (q, dq/dT) and (a, b) as
+  // pairs at 2 row and 2 row + 1; row Gr is zero (the padding of the gather lists)
+  constexpr int CR = (JAC ? 4 : 1) * (Gr + 1);           // LDS rows of one buffer
+  double* const chunk0 = lds + (size_t)L.chunk * TS + (JAC ? 2 : 1) * s;
+  const bool two = L.nbuf == 2;
   __syncthreads();
   if (g == 0) {
     // four interleaved partial sums in a fixed order (independent of the
@@ -473,10 +645,18 @@ __device__ __forceinline__ void tile_body(const MechDev& md, unsigned tile, int6
     SC[SC_CP * TS] = (c0[0] + c0[1]) + (c0[2] + c0[3]);
     SC[SC_DCP * TS] = (c1[0] + c1[1]) + (c1[2] + c1[3]);
   }
-  __syncthreads();
+  if (!L.early) __syncthreads();
+  if (g == Gr - 1)
+    for (int b = 0; b < (two ? 2 : 1); ++b) {
+      double* z = chunk0 + (size_t)(b * CR + (JAC ? 4 : 1) * Gr) * TS;
+      z[0] = 0.0;
+      if (JAC) {
+        z[1] = 0.0;
+        z[2 * TS] = z[2 * TS + 1] = 0.0;
+      }
+    }
 
   // ---- phase B: reactions in chunks of Gr, gathered per species (no atomics)
-  double* const chunk0 = lds + (size_t)L.chunk * TS + s;
   double* KF = lds + (size_t)L.KF * TS + s;
   double* KR = lds + (size_t)L.KR * TS + s;
   double* Gs = lds + (size_t)L.G * TS + s;
@@ -486,75 +666,100 @@ __device__ __forceinline__ void tile_body(const MechDev& md, unsigned tile, int6
   // With two result buffers the chunks alternate between them and one
   // barrier per chunk suffices: the barrier after chunk c's evaluation also
   // orders every gather of chunk c - 1 before chunk c + 1 overwrites that
-  // buffer.  With one, a second barrier follows the gathers.
-  const bool two = L.nbuf == 2;
+  // buffer.  With one, a second barrier follows the gathers.  What the next
+  // steps read from memory is fetched ahead: the hot half of the next chunk's
+  // record before the gathers, the gather lists' first blocks before the
+  // evaluation, the blocks' places a chunk earlier.
+  constexpr bool PF = KPT <= 2;
+  int meta[KPT];
+#pragma unroll
+  for (int q = 0; q < KPT; ++q) meta[q] = md.spg_meta[min(g + q * Gr, N - 1)];
+  int4 rw[8];
+  auto fetch = [&](int i) {
+    const int4* src = reinterpret_cast<const int4*>(md.rx + min(i, NR - 1));
+#pragma unroll
+    for (int u = 0; u < 8; ++u) rw[u] = src[u];
+  };
+  fetch(g);
   for (int c0 = 0, ch = 0; c0 < NR; c0 += Gr, ++ch) {
     const int i = c0 + g;
-    double* const chunk = chunk0 + (two ? (ch & 1) : 0) * (JAC ? 4 : 1) * Gr * TS;
-    // this chunk's gather bounds and first list entries, fetched before the
-    // reaction evaluation so that their latency overlaps it
-    const int* bnd = md.spg_chunk + (size_t)ch * N;
-    int gb0[KPT], gb1[KPT];
+    double* const chunk = chunk0 + (size_t)(two ? (ch & 1) : 0) * CR * TS;
+    GatherBlk blk[KPT];
+    int mnext[KPT];
 #pragma unroll
     for (int q = 0; q < KPT; ++q) {
-      const int k = min(g + q * Gr, N - 1);
-      gb0[q] = bnd[k];
-      gb1[q] = bnd[N + k];
+      if (PF) blk[q] = md.spg_blk[meta[q] >> 8];
+      mnext[q] = md.spg_meta[(size_t)(ch + 1) * N + min(g + q * Gr, N - 1)];
     }
     if (i < NR) {
       RxnRec Rr;
-      {   // hot half of the record: 8 independent 16-byte loads
-        const int4* src = reinterpret_cast<const int4*>(md.rx + i);
+      {
         int4* dst = reinterpret_cast<int4*>(&Rr);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) dst[u] = src[u];
+        for (int u = 0; u < 8; ++u) dst[u] = rw[u];
       }
       RxnResult o;
-      eval_reaction<TS, JAC>(md, Rr, md.rx + i, X, Bk, dBk, SC[SC_T * TS], SC[SC_IT * TS], SC[SC_LT * TS],
+      eval_reaction<TS, JAC>(md, Rr, md.rx + i, X, Bk, SC[SC_T * TS], SC[SC_IT * TS], SC[SC_LT * TS],
                              SC[SC_LP * TS], SC[SC_L10P * TS], SC[SC_RHO * TS], SC[SC_IRHO * TS],
                              SC[SC_W * TS], SC[SC_M * TS], o);
-      chunk[g * TS] = o.q;
       if (JAC) {
-        chunk[(Gr + g) * TS] = o.thT;
-        chunk[(2 * Gr + g) * TS] = o.a;
-        chunk[(3 * Gr + g) * TS] = o.b;
+        double2* c2 = reinterpret_cast<double2*>(chunk) + 2 * g * TS;
+        c2[0] = make_double2(o.q, o.thT);
+        c2[TS] = make_double2(o.a, o.b);
         KF[i * TS] = o.KF;
         KR[i * TS] = o.KR;
         if (Rr.gslot >= 0) Gs[Rr.gslot * TS] = o.G;
-      } else if (live) {
-        const int64_t io = Rr.orig;
-        if (rop_f) rop_f[io * ld + sg] = o.Rf;
-        if (rop_r) rop_r[io * ld + sg] = o.Rr;
-        if (pmod) pmod[io * ld + sg] = o.c;
-      }
-    }
-    __syncthreads();
-    // species gathers over this chunk: list entries [bnd[ch][k], bnd[ch+1][k]),
-    // fetched four at a time so their loads overlap
-#pragma unroll
-    for (int q = 0; q < KPT; ++q) {
-      const int k = g + q * Gr;
-      if (k < N) {
-        const int e1 = gb1[q];
-        for (int e = gb0[q]; e < e1; e += 4) {
-          int ent[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) ent[u] = md.spg_ent[e + u];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            if (e + u < e1) {
-              const int r = (ent[u] & 0xFFFF) - c0;
-              const double nu = (double)(ent[u] >> 16);
-              acc[q][0] += nu * chunk[r * TS];
-              if (JAC) {
-                acc[q][1] += nu * chunk[(Gr + r) * TS];
-                acc[q][2] += nu * chunk[(2 * Gr + r) * TS];
-                acc[q][3] += nu * chunk[(3 * Gr + r) * TS];
-              }
-            }
-          }
+      } else {
+        chunk[g * TS] = o.q;
+        if (live) {
+          const int64_t io = Rr.orig;
+          if (rop_f) rop_f[io * ld + sg] = o.Rf;
+          if (rop_r) rop_r[io * ld + sg] = o.Rr;
+          if (pmod) pmod[io * ld + sg] = o.c;
         }
       }
+    }
+    fetch(i + Gr);
+    __syncthreads();
+    // species gathers over this chunk: blocks of eight 16-bit entries (row of
+    // the chunk, nu), four at a time so their LDS reads overlap
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) {
+      const int nblk = (g + q * Gr < N) ? (meta[q] & 0xFF) : 0;
+      const GatherBlk* bp = md.spg_blk + (meta[q] >> 8);
+      GatherBlk cur = PF ? blk[q] : GatherBlk{0, 0, 0, 0};
+      for (int b = 0; b < nblk; ++b) {
+        if (!PF || b > 0) cur = bp[b];
+        auto four = [&](unsigned e01, unsigned e23) {
+          const unsigned ee[4] = {e01 & 0xFFFFu, e01 >> 16, e23 & 0xFFFFu, e23 >> 16};
+          if (JAC) {
+            double2 u0[4], u1[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              const double2* c2 = reinterpret_cast<const double2*>(chunk) + (ee[u] & 0x7FFu) * (2 * TS);
+              u0[u] = c2[0];
+              u1[u] = c2[TS];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              const double nu = (double)((int)(ee[u] << 16) >> 27);
+              acc[q][0] += nu * u0[u].x;
+              acc[q][1] += nu * u0[u].y;
+              acc[q][2] += nu * u1[u].x;
+              acc[q][3] += nu * u1[u].y;
+            }
+          } else {
+            double v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = chunk[(ee[u] & 0x7FFu) * TS];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) acc[q][0] += (double)((int)(ee[u] << 16) >> 27) * v[u];
+          }
+        };
+        four(cur.x, cur.y);
+        if (cur.z != (unsigned)(Gr | (Gr << 16))) four(cur.z, cur.w);
+      }
+      meta[q] = mnext[q];
     }
     if (!two) __syncthreads();
   }
@@ -562,7 +767,6 @@ __device__ __forceinline__ void tile_body(const MechDev& md, unsigned tile, int6
 
   // ---- phase C: species terms, RHS (Eqs. ode, dTdt), J[0][0] sums
   double2* WAB = reinterpret_cast<double2*>(lds + (size_t)L.WA * TS) + s;
-  double* JT = lds + (size_t)L.JT * TS + s;
   double* H = lds + (size_t)L.H * TS + s;
   double* redc = lds + (size_t)L.redC * TS + s;
   const double T = SC[SC_T * TS], iT = SC[SC_IT * TS];
@@ -584,7 +788,7 @@ __device__ __forceinline__ void tile_body(const MechDev& md, unsigned tile, int6
         const double cpk = (a[0] + T * (a[1] + T * (a[2] + T * (a[3] + a[4] * T)))) * kR * md.invW[k];
         const double JTk = Wk * acc[q][1];
         WAB[k * TS] = make_double2(Wk * (wd * W + acc[q][2]) * irho, Wk * acc[q][3] * irho);
-        JT[k * TS] = JTk;
+        if (live && k < N - 1) jac[(int64_t)((k + 1) * N) * ld + sg] = JTk;      // the temperature column
         H[k * TS] = hk;
         redc[(N + k) * TS] = (cpk - hk * icp * dcpdT) * Wk * wd * irho + hk * JTk;
       } else if (live) {
@@ -624,14 +828,12 @@ __device__ __forceinline__ void tile_body(const MechDev& md, unsigned tile, int6
   if (!JAC) return;
   __syncthreads();
 
-  // ---- phase D: temperature column, species columns with the temperature row
+  // ---- phase D: species columns with the temperature row
   const double Shw = SC[SC_SHW * TS];
   const double HA = SPLIT ? SC[SC_HA * TS] : 0.0, HB = SPLIT ? SC[SC_HB * TS] : 0.0;
-  if (live)
-    for (int k = g; k < N - 1; k += Gr) jac[(int64_t)((k + 1) * N) * ld + sg] = JT[k * TS];
   const double* aN = nasa_coeffs(md, N - 1, T);
   const double cpN = (aN[0] + T * (aN[1] + T * (aN[2] + T * (aN[3] + aN[4] * T)))) * kR * md.invW[N - 1];
-  const double* Xb = lds + (size_t)L.X * TS + s;
+  const unsigned Xb = lds_addr(lds + (size_t)L.X * TS + s);
   // temperature-row element of column j from TR = sum_k h_k J[k][j] (Sec. 3.2)
   auto finish = [&](int j, double TR) {
     const double* aj = nasa_coeffs(md, j, T);
@@ -677,14 +879,11 @@ __device__ __forceinline__ void tile_body(const MechDev& md, unsigned tile, int6
       auto batch = [&](const ColRec (&r)[kColBatch]) {
         double t[kColBatch];
 #pragma unroll
-        for (int u = 0; u < kColBatch; ++u) {
-          const int x = r[u].x;
-          t[u] = r[u].coef * Xb[r[u].src * TS] * Xb[(x & 0x7FFF) * TS] * Xb[((x >> 15) & 0x7FFF) * TS];
-        }
+        for (int u = 0; u < kColBatch; ++u) t[u] = col_term<TS>(r[u], Xb);
 #pragma unroll
         for (int u = 0; u < kColBatch; ++u) {
           val += t[u];
-          if (r[u].x & kColMark) {     // ends row k < N - 1 and opens row k + 1
+          if ((int)r[u].src < 0) {     // ends row k < N - 1 and opens row k + 1
             *outp = val;
             TR += hk * val;
             outp += rstride;
@@ -786,17 +985,14 @@ __device__ __forceinline__ void tile_body(const MechDev& md, unsigned tile, int6
       auto batch = [&](const ColRec (&r)[kColBatch]) {
         double t[kColBatch];
 #pragma unroll
-        for (int u = 0; u < kColBatch; ++u) {
-          const int x = r[u].x;
-          t[u] = r[u].coef * Xb[r[u].src * TS] * Xb[(x & 0x7FFF) * TS] * Xb[((x >> 15) & 0x7FFF) * TS];
-        }
+        for (int u = 0; u < kColBatch; ++u) t[u] = col_term<TS>(r[u], Xb);
 #pragma unroll
         for (int u = 0; u < kColBatch; ++u) {
           val += t[u];
-          if (r[u].x & kColMark) {
+          if ((int)r[u].src < 0) {
             if (k < N - 1 && live) colp[k * rstride] = val + (ab.x * vj + ab.y);
             TR += hk * val;
-            k = r[u].src;
+            k = r[u].src & 0xFFFF;
             val = 0.0;
             // k = N after the last present row: only zero terms follow, so the
             // clamped reads are never used
@@ -826,7 +1022,7 @@ __device__ __forceinline__ void tile_body(const MechDev& md, unsigned tile, int6
 }
 
 template <int TS, int NT, int KPT, bool JAC, bool SPLIT>
-__global__ __launch_bounds__(NT, tile_waves_per_eu(NT)) void tile_kernel(MechDev md, int64_t n, int64_t ld,
+__global__ __launch_bounds__(NT, tile_waves_per_eu(NT, KPT)) void tile_kernel(MechDev md, int64_t n, int64_t ld,
                                                   const double* __restrict__ phi,
                                                   const double* __restrict__ pin,
                                                   double* __restrict__ rop_f, double* __restrict__ rop_r,
@@ -842,7 +1038,7 @@ __global__ __launch_bounds__(NT, tile_waves_per_eu(NT)) void tile_kernel(MechDev
 // form and an upper bound KPT of species per thread; the dynamic LDS is the
 // largest item's).  Per state the results are those of tile_kernel.
 template <int TS, int NT, int KPT, bool SPLIT>
-__global__ __launch_bounds__(NT, tile_waves_per_eu(NT)) void tile_multi_kernel(WorkList wl) {
+__global__ __launch_bounds__(NT, tile_waves_per_eu(NT, KPT)) void tile_multi_kernel(WorkList wl) {
   const unsigned t = xcd_tile();
   int i = 0;
   while (i + 1 < wl.n_items && (int64_t)t >= wl.item[i + 1].tile0) ++i;
@@ -880,16 +1076,16 @@ struct CvLayout {
     red = H + N + 1;                    // five per-species sum terms [5][N]
     const int endC = red + 5 * N;
     auto total = [&](int nb) {
-      const int endB = chunk + nb * 4 * Gr;
+      const int endB = chunk + nb * 4 * (Gr + 1);
       return endB > endC ? endB : endC;
     };
-    nbuf = two_chunk_buffers(total(1), total(2), TS, NT) ? 2 : 1;   // as TileLayout
+    nbuf = two_chunk_buffers(N, total(1), total(2), TS, NT) ? 2 : 1;   // as TileLayout
     rows = total(nbuf);
   }
 };
 
 template <int TS, int NT, int KPT>
-__global__ __launch_bounds__(NT, tile_waves_per_eu(NT)) void conc_tile_kernel(MechDev md, int64_t n, int64_t ld,
+__global__ __launch_bounds__(NT, tile_waves_per_eu(NT, KPT)) void conc_tile_kernel(MechDev md, int64_t n, int64_t ld,
                                                                            const double* __restrict__ phi,
                                                                            double* __restrict__ out) {
   constexpr int Gr = NT / TS;
@@ -902,8 +1098,7 @@ __global__ __launch_bounds__(NT, tile_waves_per_eu(NT)) void conc_tile_kernel(Me
   const CvLayout L(N, NR, NG, TS, NT);
   double* X = lds + (size_t)L.X * TS + s;
   double* SC = lds + (size_t)L.SC * TS + s;
-  double* Bk = lds + (size_t)L.Bk * TS + s;
-  double* dBk = lds + (size_t)L.dBk * TS + s;
+  double* Bk = lds + (size_t)L.Bk * TS + 2 * s;         // (B_k, dB_k/dT) pairs
 
   // ---- phase A: concentrations are the state; p = R T sum [X] (Eq. state)
   for (int k = g; k < N; k += Gr) X[k * TS] = phi[(int64_t)(k + 1) * ld + sl];
@@ -934,77 +1129,102 @@ __global__ __launch_bounds__(NT, tile_waves_per_eu(NT)) void conc_tile_kernel(Me
   for (int k = g; k < N; k += Gr) {
     const double T = SC[SC_T * TS], iT = SC[SC_IT * TS], lT = SC[SC_LT * TS];
     const double* a = nasa_coeffs(md, k, T);
-    Bk[k * TS] = a[6] - a[0] + (a[0] - 1.0) * lT +
-                 T * (a[1] * 0.5 + T * (a[2] * (1.0 / 6.0) + T * (a[3] * (1.0 / 12.0) + a[4] * 0.05 * T))) -
-                 a[5] * iT;
-    dBk[k * TS] = (a[0] - 1.0 + a[5] * iT) * iT + a[1] * 0.5 +
-                  T * (a[2] * (1.0 / 3.0) + T * (a[3] * 0.25 + a[4] * 0.2 * T));
+    reinterpret_cast<double2*>(Bk)[k * TS] =
+        make_double2(a[6] - a[0] + (a[0] - 1.0) * lT +
+                         T * (a[1] * 0.5 + T * (a[2] * (1.0 / 6.0) + T * (a[3] * (1.0 / 12.0) + a[4] * 0.05 * T))) -
+                         a[5] * iT,
+                     (a[0] - 1.0 + a[5] * iT) * iT + a[1] * 0.5 +
+                         T * (a[2] * (1.0 / 3.0) + T * (a[3] * 0.25 + a[4] * 0.2 * T)));
   }
   __syncthreads();
 
   // ---- phase B: reactions in chunks, gathered per species (no atomics):
   // acc 0 wdot_k, 1 d wdot_k/dT, 2 u_k
-  double* const chunk0 = lds + (size_t)L.chunk * TS + s;
+  constexpr int CR = 4 * (Gr + 1);
+  double* const chunk0 = lds + (size_t)L.chunk * TS + 2 * s;    // as tile_body's in Jacobian mode
   double* KF = lds + (size_t)L.KF * TS + s;
   double* KR = lds + (size_t)L.KR * TS + s;
   double* Gs = lds + (size_t)L.G * TS + s;
   double acc[KPT][3];
 #pragma unroll
   for (int q = 0; q < KPT; ++q) acc[q][0] = acc[q][1] = acc[q][2] = 0.0;
-  // one or two result buffers, as in tile_body
+  // one or two result buffers, and everything fetched ahead as in tile_body
   const bool two = L.nbuf == 2;
+  if (g == Gr - 1)
+    for (int b = 0; b < (two ? 2 : 1); ++b) {
+      double* z = chunk0 + (size_t)(b * CR + 4 * Gr) * TS;
+      z[0] = z[1] = z[2 * TS] = z[2 * TS + 1] = 0.0;
+    }
+  constexpr bool PF = KPT <= 2;
+  int meta[KPT];
+#pragma unroll
+  for (int q = 0; q < KPT; ++q) meta[q] = md.spg_meta[min(g + q * Gr, N - 1)];
+  int4 rw[8];
+  auto fetch = [&](int i) {
+    const int4* src = reinterpret_cast<const int4*>(md.rx + min(i, NR - 1));
+#pragma unroll
+    for (int u = 0; u < 8; ++u) rw[u] = src[u];
+  };
+  fetch(g);
   for (int c0 = 0, ch = 0; c0 < NR; c0 += Gr, ++ch) {
     const int i = c0 + g;
-    double* const chunk = chunk0 + (two ? (ch & 1) : 0) * 4 * Gr * TS;
-    const int* bnd = md.spg_chunk + (size_t)ch * N;
-    int gb0[KPT], gb1[KPT];
+    double* const chunk = chunk0 + (size_t)(two ? (ch & 1) : 0) * CR * TS;
+    GatherBlk blk[KPT];
+    int mnext[KPT];
 #pragma unroll
     for (int q = 0; q < KPT; ++q) {
-      const int k = min(g + q * Gr, N - 1);
-      gb0[q] = bnd[k];
-      gb1[q] = bnd[N + k];
+      if (PF) blk[q] = md.spg_blk[meta[q] >> 8];
+      mnext[q] = md.spg_meta[(size_t)(ch + 1) * N + min(g + q * Gr, N - 1)];
     }
     if (i < NR) {
       RxnRec Rr;
       {
-        const int4* src = reinterpret_cast<const int4*>(md.rx + i);
         int4* dst = reinterpret_cast<int4*>(&Rr);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) dst[u] = src[u];
+        for (int u = 0; u < 8; ++u) dst[u] = rw[u];
       }
       RxnResult o;
-      eval_reaction<TS, true, true>(md, Rr, md.rx + i, X, Bk, dBk, SC[SC_T * TS], SC[SC_IT * TS],
+      eval_reaction<TS, true, true>(md, Rr, md.rx + i, X, Bk, SC[SC_T * TS], SC[SC_IT * TS],
                                     SC[SC_LT * TS], SC[SC_LP * TS], SC[SC_L10P * TS], 0.0, 0.0, 0.0,
                                     SC[SC_M * TS], o, SC[SC_IM * TS]);
-      chunk[g * TS] = o.q;
-      chunk[(Gr + g) * TS] = o.thT;
-      chunk[(2 * Gr + g) * TS] = o.a;
+      double2* c2 = reinterpret_cast<double2*>(chunk) + 2 * g * TS;
+      c2[0] = make_double2(o.q, o.thT);
+      c2[TS] = make_double2(o.a, 0.0);
       KF[i * TS] = o.KF;
       KR[i * TS] = o.KR;
       if (Rr.gslot >= 0) Gs[Rr.gslot * TS] = o.G;
     }
+    fetch(i + Gr);
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < KPT; ++q) {
-      const int k = g + q * Gr;
-      if (k < N) {
-        const int e1 = gb1[q];
-        for (int e = gb0[q]; e < e1; e += 4) {
-          int ent[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) ent[u] = md.spg_ent[e + u];
+      const int nblk = (g + q * Gr < N) ? (meta[q] & 0xFF) : 0;
+      const GatherBlk* bp = md.spg_blk + (meta[q] >> 8);
+      GatherBlk cur = PF ? blk[q] : GatherBlk{0, 0, 0, 0};
+      for (int b = 0; b < nblk; ++b) {
+        if (!PF || b > 0) cur = bp[b];
+        auto four = [&](unsigned e01, unsigned e23) {
+          const unsigned ee[4] = {e01 & 0xFFFFu, e01 >> 16, e23 & 0xFFFFu, e23 >> 16};
+          double2 u0[4];
+          double u1[4];
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
-            if (e + u < e1) {
-              const int r = (ent[u] & 0xFFFF) - c0;
-              const double nu = (double)(ent[u] >> 16);
-              acc[q][0] += nu * chunk[r * TS];
-              acc[q][1] += nu * chunk[(Gr + r) * TS];
-              acc[q][2] += nu * chunk[(2 * Gr + r) * TS];
-            }
+            const double2* c2 = reinterpret_cast<const double2*>(chunk) + (ee[u] & 0x7FFu) * (2 * TS);
+            u0[u] = c2[0];
+            u1[u] = c2[TS].x;
           }
-        }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const double nu = (double)((int)(ee[u] << 16) >> 27);
+            acc[q][0] += nu * u0[u].x;
+            acc[q][1] += nu * u0[u].y;
+            acc[q][2] += nu * u1[u];
+          }
+        };
+        four(cur.x, cur.y);
+        if (cur.z != (unsigned)(Gr | (Gr << 16))) four(cur.z, cur.w);
       }
+      meta[q] = mnext[q];
     }
     if (!two) __syncthreads();
   }
@@ -1064,7 +1284,7 @@ __global__ __launch_bounds__(NT, tile_waves_per_eu(NT)) void conc_tile_kernel(Me
 
   // ---- phase D: sparse part, one column stream per group (present rows)
   const double T = SC[SC_T * TS];
-  const double* Xb = lds + (size_t)L.X * TS + s;
+  const unsigned Xb = lds_addr(lds + (size_t)L.X * TS + s);
   for (int jc = g; jc < N; jc += Gr) {
     const int j = md.cv_col_order[jc];
     const ColRec* rec = md.cv_colrec + md.cv_col_start[j];
@@ -1076,20 +1296,17 @@ __global__ __launch_bounds__(NT, tile_waves_per_eu(NT)) void conc_tile_kernel(Me
     auto batch = [&](const ColRec (&r)[kColBatch]) {
       double t[kColBatch];
 #pragma unroll
-      for (int u = 0; u < kColBatch; ++u) {
-        const int x = r[u].x;
-        t[u] = r[u].coef * Xb[r[u].src * TS] * Xb[(x & 0x7FFF) * TS] * Xb[((x >> 15) & 0x7FFF) * TS];
-      }
+      for (int u = 0; u < kColBatch; ++u) t[u] = col_term<TS>(r[u], Xb);
 #pragma unroll
       for (int u = 0; u < kColBatch; ++u) {
         val += t[u];
-        if (r[u].x & kColMark) {       // ends the open row (if any), opens row src
+        if ((int)r[u].src < 0) {       // ends the open row (if any), opens row src
           if (k < N) {
             *outp = val;
             outp += ld;
             TR += hk * val;
           }
-          k = r[u].src;
+          k = r[u].src & 0xFFFF;
           val = 0.0;
           hk = H[k * TS];              // row N: slack, never used
         }

@@ -281,6 +281,10 @@ uint64_t fnv1a(const std::string& s) {
   return h;
 }
 
+ColRec col_rec(double coef, int src, uint32_t x, bool mark = false) {
+  return ColRec{coef, (uint32_t)src | (mark ? kColMark : 0u), x};
+}
+
 int pack_side(int sp, int nu) { return sp | (nu << 16); }
 
 // A piece of a Jacobian column stream: rows [k0, k1) of column j, len records.
@@ -406,7 +410,8 @@ int build_tables(const std::string& text, PackedMech& P, std::string& msg) {
         rec.net[c++] = pack_side(k, nu & 0xFFFF);
         dnu += nu;
       }
-      for (; c < kMaxNet; ++c) rec.net[c] = -1;
+      // unused entries: nu = 0 of a species of the reaction
+      for (; c < kMaxNet; ++c) rec.net[c] = rec.mol[0];
       rec.dnu_lnpr = dnu * lnpr;
       // Arrhenius: primary rate coefficient (k_f), secondary ratio k0/kinf, reverse
       if (r.cls == K_ELEM || r.cls == K_THD) { rec.arr[0] = r.arr.A; rec.arr[1] = r.arr.b; rec.arr[2] = r.arr.Ta; }
@@ -484,11 +489,10 @@ int build_tables(const std::string& text, PackedMech& P, std::string& msg) {
       for (auto& e : lists[k]) P.spg_ent.push_back(e.first | ((int)e.second << 16));
       P.spg_ptr.push_back((int)P.spg_ent.size());
     }
-    P.spg_ent.resize(P.spg_ent.size() + 4, 0);      // slack for the unrolled gather
     // ---- Jacobian column streams.  For species row k and species column j the
     // j-specific part of J[k+1][j+1] is sum_t coef_t * P[src_t] * X[x1_t] * X[x2_t]
     // with P = {c_i k_f,i (slots 0..NR-1), c_i k_r,i (NR..2NR-1), dc_i/dE_i * R_i (2NR..)}.
-    struct Term { int j, k, src, x; double coef; };
+    struct Term { int j, k, src; uint32_t x; double coef; };
     std::vector<Term> terms;
     auto cofactors = [&](const std::vector<std::pair<int, int>>& sidev, int l) {
       // molecules of the side other than one copy of species l; N means "1"
@@ -500,7 +504,7 @@ int build_tables(const std::string& text, PackedMech& P, std::string& msg) {
           mol.push_back(q.first);
         }
       while (mol.size() < 2) mol.push_back(N);
-      return mol[0] | (mol[1] << 15);
+      return (uint32_t)(mol[0] | (mol[1] << 16));
     };
     for (int slot = 0; slot < NR; ++slot) {
       const RawRxn& r = m.rxn[order[slot]];
@@ -524,10 +528,10 @@ int build_tables(const std::string& text, PackedMech& P, std::string& msg) {
         if (r.coll == C_EFF) {
           for (auto& [l, a] : r.eff) {
             if (l == N - 1 || a == 1.0) continue;
-            terms.push_back({l, k, 2 * NR + g, N | (N << 15), m.W[k] / m.W[l] * nu_k * (a - 1.0)});
+            terms.push_back({l, k, 2 * NR + g, (uint32_t)(N | (N << 16)), m.W[k] / m.W[l] * nu_k * (a - 1.0)});
           }
         } else if (r.coll == C_SPECIES && r.m != N - 1) {
-          terms.push_back({r.m, k, 2 * NR + g, N | (N << 15), m.W[k] / m.W[r.m] * nu_k});
+          terms.push_back({r.m, k, 2 * NR + g, (uint32_t)(N | (N << 16)), m.W[k] / m.W[r.m] * nu_k});
         }
       }
     }
@@ -552,11 +556,11 @@ int build_tables(const std::string& text, PackedMech& P, std::string& msg) {
       // the stream); markers and padding address X[N] = 1 and contribute 0
       std::vector<std::vector<std::vector<ColRec>>> rows(N - 1, std::vector<std::vector<ColRec>>(N));
       for (size_t t = 0; t < terms.size(); ++t)
-        rows[terms[t].j][terms[t].k].push_back(ColRec{terms[t].coef, N + 1 + terms[t].src, terms[t].x});
+        rows[terms[t].j][terms[t].k].push_back(col_rec(terms[t].coef, N + 1 + terms[t].src, terms[t].x));
       for (int j = 0; j < N - 1; ++j)
         for (int k = 0; k < N - 1; ++k) {
-          if (rows[j][k].empty()) rows[j][k].push_back(ColRec{0.0, N, N | (N << 15)});
-          rows[j][k].back().x |= kColMark;
+          if (rows[j][k].empty()) rows[j][k].push_back(col_rec(0.0, N, N | (N << 16)));
+          rows[j][k].back().src |= kColMark;
         }
       const std::vector<ColSeg> segs = split_columns(rows, N);
       // emission: each column's segments in row order, each padded to a
@@ -576,7 +580,7 @@ int build_tables(const std::string& text, PackedMech& P, std::string& msg) {
           const int rec = (int)P.colrec.size();
           for (int k = mine[q].k0; k < mine[q].k1; ++k)
             P.colrec.insert(P.colrec.end(), rows[j][k].begin(), rows[j][k].end());
-          while (P.colrec.size() % kColBatch) P.colrec.push_back(ColRec{0.0, N, N | (N << 15)});
+          while (P.colrec.size() % kColBatch) P.colrec.push_back(col_rec(0.0, N, N | (N << 16)));
           P.col_item.push_back(ColItem{j, mine[q].k0, rec, (int)P.colrec.size() - rec, joined ? slot++ : -1,
                                        mine[q].k1 == N ? 1 : 0, 0, 0});
         }
@@ -586,7 +590,7 @@ int build_tables(const std::string& text, PackedMech& P, std::string& msg) {
                        [](const ColItem& a, const ColItem& b) { return a.cnt > b.cnt; });
       P.col_start.push_back((int)P.colrec.size());
       // one batch of slack: the kernel reads one batch past a segment's stream
-      for (int u = 0; u < kColBatch; ++u) P.colrec.push_back(ColRec{0.0, N, N | (N << 15)});
+      for (int u = 0; u < kColBatch; ++u) P.colrec.push_back(col_rec(0.0, N, N | (N << 16)));
     } else {
       size_t t = 0;
       for (int j = 0; j < N - 1; ++j) {
@@ -609,19 +613,19 @@ int build_tables(const std::string& text, PackedMech& P, std::string& msg) {
               P.col_flags[(size_t)j * FW + w] |= 1u << (k - k0);
             }
         }
-        P.colrec.push_back(ColRec{0.0, rows.empty() ? N : rows[0], N | (N << 15) | kColMark});
+        P.colrec.push_back(col_rec(0.0, rows.empty() ? N : rows[0], N | (N << 16), true));
         for (size_t q = 0; q < rows.size(); ++q) {
           for (; t < terms.size() && terms[t].j == j && terms[t].k == rows[q]; ++t)
-            P.colrec.push_back(ColRec{terms[t].coef, N + 1 + terms[t].src, terms[t].x});
+            P.colrec.push_back(col_rec(terms[t].coef, N + 1 + terms[t].src, terms[t].x));
           const int next = q + 1 < rows.size() ? rows[q + 1] : N;
-          P.colrec.push_back(ColRec{0.0, next, N | (N << 15) | kColMark});
+          P.colrec.push_back(col_rec(0.0, next, N | (N << 16), true));
         }
         // padding addresses X[N] = 1 and contributes 0
-        while (P.colrec.size() % (2 * kColBatch)) P.colrec.push_back(ColRec{0.0, N, N | (N << 15)});
+        while (P.colrec.size() % (2 * kColBatch)) P.colrec.push_back(col_rec(0.0, N, N | (N << 16)));
       }
       P.col_start.push_back((int)P.colrec.size());
       // one batch of slack: the kernel reads one batch past a column's stream
-      for (int u = 0; u < kColBatch; ++u) P.colrec.push_back(ColRec{0.0, N, N | (N << 15)});
+      for (int u = 0; u < kColBatch; ++u) P.colrec.push_back(col_rec(0.0, N, N | (N << 16)));
     }
     // ---- concentration-based, constant-volume form (state {T, [X_1..X_N]}):
     // d wdot_k / d[X_l] = sum_i nu_ki dq_i/d[X_l]; the mass-action and
@@ -644,9 +648,9 @@ int build_tables(const std::string& text, PackedMech& P, std::string& msg) {
           const int g = P.rx[slot].gslot;
           if (r.coll == C_EFF) {
             for (auto& [l, a] : r.eff)
-              if (a != 1.0) tv.push_back({l, k, 2 * NR + g, N | (N << 15), nu_k * (a - 1.0)});
+              if (a != 1.0) tv.push_back({l, k, 2 * NR + g, (uint32_t)(N | (N << 16)), nu_k * (a - 1.0)});
           } else if (r.coll == C_SPECIES) {
-            tv.push_back({r.m, k, 2 * NR + g, N | (N << 15), (double)nu_k});
+            tv.push_back({r.m, k, 2 * NR + g, (uint32_t)(N | (N << 16)), (double)nu_k});
           }
         }
       }
@@ -662,17 +666,17 @@ int build_tables(const std::string& text, PackedMech& P, std::string& msg) {
           if (rows.empty() || rows.back() != tv[u].k) rows.push_back(tv[u].k);
         for (int k : rows) P.cv_rowidx.push_back(k);
         P.cv_colptr.push_back((int)P.cv_rowidx.size());
-        P.cv_colrec.push_back(ColRec{0.0, rows.empty() ? N : rows[0], N | (N << 15) | kColMark});
+        P.cv_colrec.push_back(col_rec(0.0, rows.empty() ? N : rows[0], N | (N << 16), true));
         for (size_t q = 0; q < rows.size(); ++q) {
           for (; t < tv.size() && tv[t].j == j && tv[t].k == rows[q]; ++t)
-            P.cv_colrec.push_back(ColRec{tv[t].coef, N + 1 + tv[t].src, tv[t].x});
+            P.cv_colrec.push_back(col_rec(tv[t].coef, N + 1 + tv[t].src, tv[t].x));
           const int next = q + 1 < rows.size() ? rows[q + 1] : N;
-          P.cv_colrec.push_back(ColRec{0.0, next, N | (N << 15) | kColMark});
+          P.cv_colrec.push_back(col_rec(0.0, next, N | (N << 16), true));
         }
-        while (P.cv_colrec.size() % (2 * kColBatch)) P.cv_colrec.push_back(ColRec{0.0, N, N | (N << 15)});
+        while (P.cv_colrec.size() % (2 * kColBatch)) P.cv_colrec.push_back(col_rec(0.0, N, N | (N << 16)));
       }
       P.cv_col_start.push_back((int)P.cv_colrec.size());
-      for (int u = 0; u < kColBatch; ++u) P.cv_colrec.push_back(ColRec{0.0, N, N | (N << 15)});
+      for (int u = 0; u < kColBatch; ++u) P.cv_colrec.push_back(col_rec(0.0, N, N | (N << 16)));
       P.cv_col_order.resize(N);
       std::iota(P.cv_col_order.begin(), P.cv_col_order.end(), 0);
       std::stable_sort(P.cv_col_order.begin(), P.cv_col_order.end(), [&](int a, int b) {
@@ -697,19 +701,25 @@ int build_tables(const std::string& text, PackedMech& P, std::string& msg) {
   }
 }
 
-std::vector<int> species_chunk_bounds(const PackedMech& P, int chunk) {
-  const int N = P.N;
-  const int nch = (P.NR + chunk - 1) / chunk;
-  std::vector<int> b((size_t)(nch + 1) * N);
-  for (int k = 0; k < N; ++k) {
-    int e = P.spg_ptr[k];
-    for (int c = 0; c <= nch; ++c) {
-      const int lim = c * chunk;
-      while (e < P.spg_ptr[k + 1] && (P.spg_ent[e] & 0xFFFF) < lim) ++e;
-      b[(size_t)c * N + k] = e;
+GatherLists gather_lists(const PackedMech& P, int chunk) {
+  const int N = P.N, nch = (P.NR + chunk - 1) / chunk;
+  GatherLists G;
+  G.meta.assign((size_t)(nch + 1) * N, 0);
+  const uint16_t pad = (uint16_t)chunk;
+  std::vector<int> at(P.spg_ptr.begin(), P.spg_ptr.end() - 1);
+  for (int c = 0; c < nch; ++c)
+    for (int k = 0; k < N; ++k) {
+      const int first = (int)G.blk.size() / 8;
+      for (; at[k] < P.spg_ptr[k + 1] && (P.spg_ent[at[k]] & 0xFFFF) < (c + 1) * chunk; ++at[k]) {
+        const int slot = P.spg_ent[at[k]] & 0xFFFF, nu = P.spg_ent[at[k]] >> 16;
+        G.blk.push_back((uint16_t)((slot - c * chunk) | ((nu & 0x1F) << 11)));
+      }
+      while (G.blk.size() % 8) G.blk.push_back(pad);
+      const int n = (int)G.blk.size() / 8 - first;
+      G.meta[(size_t)c * N + k] = n ? (first << 8) | n : 0;
     }
-  }
-  return b;
+  for (int u = 0; u < 8; ++u) G.blk.push_back(pad);
+  return G;
 }
 
 }  // namespace pyjac

@@ -53,10 +53,10 @@ struct alignas(16) RxnRec {
 static_assert(sizeof(RxnRec) == 256, "RxnRec must stay 256 bytes");
 
 // One entry of a Jacobian column stream.  Every entry contributes
-// coef * X[src] * X[x & 0x7FFF] * X[(x >> 15) & 0x7FFF] to the current element,
+// coef * X[src & 0xFFFF] * X[x & 0xFFFF] * X[x >> 16] to the current element,
 // where X[0..N] are the concentrations (X[N] = 1) and the rate products P
 // follow directly, so src = N + 1 + (index into P).  An entry with bit
-// kColMark set in x ends a row after its own contribution; a marker is such an
+// kColMark set in src ends a row after its own contribution; a marker is such an
 // entry with coef = 0; padding has coef = 0 and src = N.  Two forms:
 //  * every row (col_split = 0): for rows k = 0..N-1 in order, the terms of
 //    (k, j); for k < N - 1 the row's last term carries the mark, and a row
@@ -72,9 +72,9 @@ static_assert(sizeof(RxnRec) == 256, "RxnRec must stay 256 bytes");
 // terms (large mechanisms), where it saves a marker per empty row.
 struct alignas(16) ColRec {
   double coef;
-  int src, x;
+  uint32_t src, x;
 };
-constexpr int kColMark = 1 << 30;
+constexpr uint32_t kColMark = 1u << 31;
 constexpr int kColBatch = 4;
 
 // Every-row form: a column's stream may be cut at row boundaries into
@@ -123,10 +123,20 @@ struct PackedMech {
 
 constexpr int colFlagWords(int N) { return (N + 31) / 32; }
 
-// Per-chunk bounds of the species reaction lists for reaction chunks of size
-// `chunk`: entry [c * N + k] is the first list index of species k whose
-// reaction slot is >= c * chunk; there are ceil(NR / chunk) + 1 rows.
-std::vector<int> species_chunk_bounds(const PackedMech& P, int chunk);
+// Gather lists of one launch shape: the species reaction lists cut into
+// reaction chunks of size `chunk`.  An entry is 16 bits, the reaction's row in
+// the chunk (low 11 bits) and nu (signed, high 5); entries come in blocks of
+// eight (16 bytes), padded with row `chunk` (a row of zeros) and nu = 0.
+// meta[c * N + k] = first block << 8 | number of blocks, with one more row of
+// zeros after the last chunk; `blk` holds at least one block.
+struct alignas(16) GatherBlk {
+  uint32_t x, y, z, w;
+};
+struct GatherLists {
+  std::vector<int> meta;
+  std::vector<uint16_t> blk;
+};
+GatherLists gather_lists(const PackedMech& P, int chunk);
 
 // Parse + validate + pack.  Returns 0 or a PYJAC_E_* code with msg set.
 int build_tables(const std::string& text, PackedMech& out, std::string& msg);
@@ -145,8 +155,8 @@ struct MechDev {
   const double* __restrict__ eff_am1;
   const double* __restrict__ plog;
   const double* __restrict__ cheb;
-  const int* __restrict__ spg_ent;
-  const int* __restrict__ spg_chunk;    // species_chunk_bounds for the launch's chunk size
+  const int* __restrict__ spg_meta;     // GatherLists of the launch's chunk size
+  const GatherBlk* __restrict__ spg_blk;
   const int* __restrict__ col_start;    // [N]
   const ColRec* __restrict__ colrec;
   const int* __restrict__ col_order;    // [N-1] longest column stream first
