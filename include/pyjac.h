@@ -325,7 +325,8 @@ pyjac_status pyjac_newton_factor_solve_noalloc(const pyjac_mech* mech, int64_t n
  * (which = 0: rates kernel, 1: Jacobian kernel, 2: concentration-form
  * Jacobian) to tile_states states per
  * workgroup and `threads` threads per workgroup; tile_states = 0 restores the
- * automatic choice (largest tile whose LDS working set fits the device).
+ * automatic choice, which single-mechanism calls make by the batch's size
+ * (work lists then take the largest tile whose LDS working set fits the device).
  * Results per state do not depend on the shape (all per-state sums run in
  * species order).  Not thread-safe against
  * concurrent evaluation calls on the same handle.  Errors: PYJAC_E_INVALID,
@@ -354,7 +355,8 @@ pyjac_status pyjac_mech_autotune(pyjac_mech* mech, int32_t which, int64_t n_stat
                                  int32_t* shapes, float* ms, int32_t max_entries,
                                  int32_t* n_entries, void* stream);
 
-/* Current launch shape of a kernel family and its dynamic LDS bytes. */
+/* Launch shape of a kernel family and its dynamic LDS bytes: the one set or
+ * tuned, otherwise the one of work lists. */
 pyjac_status pyjac_mech_get_variant(const pyjac_mech* mech, int32_t which, int32_t* tile_states,
                                     int32_t* threads, size_t* lds_bytes);
 

@@ -4,6 +4,7 @@
 
 #include <cstdlib>
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <fstream>
 #include <mutex>
@@ -55,15 +56,14 @@ struct pyjac_mech {
   int device = 0;
   size_t max_lds = 65536;
   pyjac::Variant jac_var, rates_var, conc_var;
-  // per launch shape: gather lists, built when the shape is chosen
-  struct VarDev {
-    int ts = 0, nt = 0;
-    bool jac = false;
-    void* mem = nullptr;
+  bool fixed[3] = {false, false, false};      // rates, Jacobian, concentration form: shape set or tuned
+  pyjac::Variant big[3];                      // shapes of large batches (big_shape)
+  int cus = 256;
+  // gather lists by reaction-chunk size 16, 32, ..., 512 (threads / tile states)
+  struct Lists {
     const int* meta = nullptr;
     const pyjac::GatherBlk* blk = nullptr;
-  };
-  std::vector<VarDev> vars;
+  } lists[6];
 };
 
 namespace pyjac {
@@ -127,6 +127,11 @@ pyjac_status upload(pyjac_mech* m) {
   append(blob, P.col_item, o); append(blob, P.col_join, o);
   append(blob, P.cv_col_start, o); append(blob, P.cv_colrec, o); append(blob, P.cv_col_order, o);
   append(blob, P.cv_colptr, o);
+  for (int q = 0; q < 6; ++q) {
+    const GatherLists G = gather_lists(P, 16 << q);
+    append(blob, G.meta, o);
+    append(blob, G.blk, o);
+  }
   if (hipMalloc(&m->dmem, blob.size()) != hipSuccess) return fail(PYJAC_E_NOMEM, "hipMalloc of mechanism tables failed");
   if (hipMemcpy(m->dmem, blob.data(), blob.size(), hipMemcpyHostToDevice) != hipSuccess)
     return fail(PYJAC_E_DEVICE, "copy of mechanism tables failed");
@@ -146,44 +151,94 @@ pyjac_status upload(pyjac_mech* m) {
   d.n_col_item = (int)P.col_item.size(); d.n_col_join = (int)P.col_join.size();
   d.cv_col_start = D((const int*)0); d.cv_colrec = D((const ColRec*)0); d.cv_col_order = D((const int*)0);
   d.cv_colptr = D((const int*)0);
+  for (auto& l : m->lists) {
+    l.meta = D((const int*)0);
+    l.blk = D((const GatherBlk*)0);
+  }
   d.spg_meta = nullptr;
   d.spg_blk = nullptr;
   return PYJAC_OK;
 }
 
-// Device data of one launch shape (built once per shape and kernel family).
-pyjac_status ensure_var(pyjac_mech* m, Variant v, bool jac) {
-  for (auto& e : m->vars) if (e.ts == v.ts && e.nt == v.nt && e.jac == jac) return PYJAC_OK;
-  pyjac_mech::VarDev vd;
-  vd.ts = v.ts; vd.nt = v.nt; vd.jac = jac;
-  std::vector<char> blob;
-  std::vector<size_t> o;
-  const GatherLists G = gather_lists(m->host, v.nt / v.ts);
-  append(blob, G.meta, o);
-  append(blob, G.blk, o);
-  int prev = 0;
-  hipGetDevice(&prev);
-  hipSetDevice(m->device);
-  hipError_t e1 = hipMalloc(&vd.mem, blob.size());
-  hipError_t e2 = e1 == hipSuccess ? hipMemcpy(vd.mem, blob.data(), blob.size(), hipMemcpyHostToDevice) : e1;
-  hipSetDevice(prev);
-  if (e1 != hipSuccess) return fail(PYJAC_E_NOMEM, "hipMalloc of launch tables failed");
-  if (e2 != hipSuccess) { hipFree(vd.mem); return fail(PYJAC_E_DEVICE, "copy of launch tables failed"); }
-  char* b = static_cast<char*>(vd.mem);
-  vd.meta = reinterpret_cast<const int*>(b + o[0]);
-  vd.blk = reinterpret_cast<const GatherBlk*>(b + o[1]);
-  m->vars.push_back(vd);
-  return PYJAC_OK;
+MechDev launch_view(const pyjac_mech* m, Variant v) {
+  MechDev md = m->dev;
+  int q = 0;
+  while ((16 << q) < v.nt / v.ts) ++q;
+  md.spg_meta = m->lists[q].meta;
+  md.spg_blk = m->lists[q].blk;
+  return md;
 }
 
-MechDev launch_view(const pyjac_mech* m, Variant v, bool jac) {
-  MechDev md = m->dev;
-  for (auto& e : m->vars)
-    if (e.ts == v.ts && e.nt == v.nt && e.jac == jac) {
-      md.spg_meta = e.meta;
-      md.spg_blk = e.blk;
+bool fits(const pyjac_mech* m, int which, Variant v) {
+  return kpt_of(m->host.N, v.ts, v.nt) <= 8 && kind_lds(m, which, v) <= m->max_lds;
+}
+
+// Every compiled shape of the rates and Jacobian kernels.
+const int kShapes[][2] = {{16, 1024}, {16, 512}, {32, 1024}, {64, 1024}, {8, 512}, {8, 1024},
+                          {4, 512},   {4, 1024}, {2, 512},   {2, 1024},  {8, 256}, {4, 256}};
+
+// Shape of a batch that fills the device, when none was set or tuned.
+// Rates: as many groups per state as the largest power of two in N (at least
+// 16), so that a species' gather has one group or two.  Jacobians: the most
+// wavefronts per CU (registers and LDS), weighted down by the groups that have
+// no species; the smaller workgroup wins a tie.  us per batch, this rule's
+// shape against the widest tile that fits: RHS 418 / 441 (53 species, 100,000
+// states), 222 / 253 (111, 20,001); Jacobian 141 / 315 (13, 100,000),
+// 1,297 / 1,531 (53, 100,000), 1,079 / 1,311 (80, 40,000), 1,269 / 1,263 (111,
+// 20,001), 1,603 / 1,603 (360, 2,051).
+Variant big_shape(const pyjac_mech* m, int which) {
+  const PackedMech& P = m->host;
+  Variant best{0, 0};
+  if (which == 0) {
+    int gr = 16;
+    while (2 * gr <= P.N && gr < 512) gr *= 2;
+    for (int nt : {512, 1024, 256})
+      for (auto& q : kShapes)
+        if (!best.ts && q[1] == nt && q[1] / q[0] == gr && fits(m, which, Variant{q[0], q[1]})) best = {q[0], q[1]};
+    return best;
+  }
+  double top = 0.0;
+  auto look = [&](int ts, int nt) {
+    const Variant v{ts, nt};
+    if (!fits(m, which, v)) return;
+    const int gr = nt / ts;
+    const int by_regs = (nt == 256 && P.N > gr ? 12 : 16) / (nt / 64), by_lds = (int)(163840 / kind_lds(m, which, v));
+    const double score = std::min(by_regs, by_lds) * (nt / 64) * std::sqrt(std::min(1.0, (double)P.N / gr));
+    if (score > 1.001 * top || (score > 0.999 * top && nt < best.nt)) {
+      top = score;
+      best = v;
     }
-  return md;
+  };
+  if (which == 1) for (auto& q : kShapes) look(q[0], q[1]);
+  else for (auto& q : kConcShapes) look(q[0], q[1]);
+  return best;
+}
+
+// The shape of a call: the one set or tuned, otherwise by the batch.  A batch
+// too small to give every CU a tile takes the narrowest tiles that leave at
+// most one per CU, with enough threads for a group per reaction where the
+// shape is compiled, because its time is one tile's latency.  1,000 states of
+// 53 species: RHS 15 us (4 x 1,024) against 65 (64 x 1,024), Jacobian 31
+// against 60 (16 x 1,024); 500 of 111: 21 against 86 and 52 against 104.  Two
+// states per tile only where a chunk of 64 reactions is not all of them: 13
+// species run alike at every shape (15 to 18 us).
+Variant shape_for(const pyjac_mech* m, int which, int64_t n) {
+  const Variant set = which == 2 ? m->conc_var : which == 1 ? m->jac_var : m->rates_var;
+  if (m->fixed[which]) return set;
+  const int NR = m->host.NR;
+  for (int ts = NR > 64 ? 2 : 4; ts <= (which == 0 ? 16 : 8); ts *= 2) {
+    if ((n + ts - 1) / ts > m->cus) continue;
+    Variant v{0, 0};
+    auto look = [&](int qts, int qnt) {
+      if (qts != ts || !fits(m, which, Variant{qts, qnt})) return;
+      const bool all = qnt / ts >= NR, had = v.ts && v.nt / ts >= NR;
+      if (!v.ts || (all ? !had || qnt < v.nt : !had && qnt > v.nt)) v = {qts, qnt};
+    };
+    if (which == 2) for (auto& q : kConcShapes) look(q[0], q[1]);
+    else for (auto& q : kShapes) look(q[0], q[1]);
+    if (v.ts) return v;
+  }
+  return m->big[which].ts ? m->big[which] : set;
 }
 
 bool misaligned(const void* p) { return p && (reinterpret_cast<uintptr_t>(p) & 7u); }
@@ -243,13 +298,9 @@ pyjac_status pyjac_mech_load_string(const char* text, int32_t hip_device, pyjac_
     return fail(PYJAC_E_UNSUPPORTED, "mechanism too large for the per-tile LDS budget");
   }
   m->conc_var = pick_conc(m->host, m->max_lds);   // {0, 0}: the concentration form does not fit
-  rc = ensure_var(m, m->jac_var, true);
-  if (rc == PYJAC_OK) rc = ensure_var(m, m->rates_var, false);
-  if (rc == PYJAC_OK && m->conc_var.ts) rc = ensure_var(m, m->conc_var, true);
-  if (rc != PYJAC_OK) {
-    pyjac_mech_free(m);
-    return rc;
-  }
+  int cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, hip_device) == hipSuccess && cus > 0) m->cus = cus;
+  for (int w = 0; w < 3; ++w) m->big[w] = big_shape(m, w);
   *out = m;
   return PYJAC_OK;
 }
@@ -315,7 +366,6 @@ pyjac_status pyjac_mech_free(pyjac_mech* m) {
   hipSetDevice(m->device);
   hipDeviceSynchronize();
   if (m->dmem) hipFree(m->dmem);
-  for (auto& e : m->vars) hipFree(e.mem);
   hipSetDevice(prev);
   delete m;
   return PYJAC_OK;
@@ -329,9 +379,9 @@ pyjac_status pyjac_eval_rates(const pyjac_mech* m, int64_t n, int64_t ld, const 
   for (const double* q : {rop_f, rop_r, pres_mod, wdot, dphi})
     if (misaligned(q)) return fail(PYJAC_E_INVALID, "output pointer not 8-byte aligned");
   if (n == 0) return PYJAC_OK;
-  const Variant v = m->rates_var;
+  const Variant v = shape_for(m, 0, n);
   size_t lds = tile_lds_bytes(m->host.N, m->host.NR, m->host.NG, v.ts, v.nt, false);
-  const MechDev md = launch_view(m, v, false);
+  const MechDev md = launch_view(m, v);
   hipError_t e = launch_tile(false, v.ts, v.nt, md, n, ld, phi, p, rop_f, rop_r, pres_mod, wdot, dphi,
                              nullptr, lds, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return fail(PYJAC_E_DEVICE, std::string("rates launch failed: ") + hipGetErrorString(e));
@@ -345,9 +395,9 @@ pyjac_status pyjac_eval_jacobian(const pyjac_mech* m, int64_t n, int64_t ld, con
   if (n > 0 && !jac) return fail(PYJAC_E_INVALID, "jac is NULL");
   if (misaligned(jac)) return fail(PYJAC_E_INVALID, "jac not 8-byte aligned");
   if (n == 0) return PYJAC_OK;
-  const Variant v = m->jac_var;
+  const Variant v = shape_for(m, 1, n);
   size_t lds = tile_lds_bytes(m->host.N, m->host.NR, m->host.NG, v.ts, v.nt, true);
-  const MechDev md = launch_view(m, v, true);
+  const MechDev md = launch_view(m, v);
   hipError_t e = launch_tile(true, v.ts, v.nt, md, n, ld, phi, p, nullptr, nullptr, nullptr, nullptr,
                              nullptr, jac, lds, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return fail(PYJAC_E_DEVICE, std::string("jacobian launch failed: ") + hipGetErrorString(e));
@@ -386,7 +436,7 @@ pyjac_status pyjac_eval_jacobian_multi(int32_t n_items, const pyjac_work_item* i
       if (it.n_states == 0) continue;
       const PackedMech& P = it.mech->host;
       WorkItem& w = wl.item[c++];
-      w.md = launch_view(it.mech, v, true);
+      w.md = launch_view(it.mech, v);
       w.phi = it.phi;
       w.p = it.p;
       w.jac = it.jac;
@@ -428,10 +478,10 @@ pyjac_status pyjac_eval_jacobian_conc(const pyjac_mech* m, int64_t n, int64_t ld
   if (hipGetDevice(&cur) != hipSuccess || cur != m->device)
     return fail(PYJAC_E_INVALID, "current HIP device differs from the mechanism's device");
   if (ld > (int64_t)1 << 40) return fail(PYJAC_E_INVALID, "ld too large");
-  const Variant v = m->conc_var;
-  if (!v.ts) return fail(PYJAC_E_UNSUPPORTED, "mechanism too large for the concentration-form tile");
+  if (!m->conc_var.ts) return fail(PYJAC_E_UNSUPPORTED, "mechanism too large for the concentration-form tile");
+  const Variant v = shape_for(m, 2, n);
   const size_t lds = conc_lds_bytes(m->host.N, m->host.NR, m->host.NG, v.ts, v.nt);
-  const MechDev md = launch_view(m, v, true);
+  const MechDev md = launch_view(m, v);
   hipError_t e = launch_conc(v.ts, v.nt, md, n, ld, phi_c, jac, lds, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return fail(PYJAC_E_DEVICE, std::string("jacobian launch failed: ") + hipGetErrorString(e));
   return PYJAC_OK;
@@ -487,9 +537,9 @@ pyjac_status pyjac_eval_jacobian_fd(const pyjac_mech* m, int64_t n, int64_t ld, 
   if (!workspace || workspace_bytes < per + 1024) return fail(PYJAC_E_WORKSPACE, "workspace smaller than one state");
   const int64_t chunk = std::min<int64_t>(n, (int64_t)((workspace_bytes - 1024) / per));
   const hipStream_t st = static_cast<hipStream_t>(stream);
-  const Variant v = m->rates_var;
+  const Variant v = shape_for(m, 0, chunk * (N + 1));
   const size_t lds = tile_lds_bytes(N, m->host.NR, m->host.NG, v.ts, v.nt, false);
-  const MechDev md = launch_view(m, v, false);
+  const MechDev md = launch_view(m, v);
   auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
   for (int64_t s0 = 0; s0 < n; s0 += chunk) {
     const int64_t mm = std::min(chunk, n - s0), ld2 = mm * (N + 1);
@@ -525,11 +575,8 @@ pyjac_status pyjac_mech_set_variant(pyjac_mech* m, int32_t which, int32_t ts, in
       if (!found) return fail(PYJAC_E_UNSUPPORTED, "variant not compiled");
       if (!conc_fits(m->host, v, m->max_lds)) return fail(PYJAC_E_UNSUPPORTED, "variant does not fit");
     }
-    if (v.ts) {
-      pyjac_status rc = ensure_var(m, v, true);
-      if (rc != PYJAC_OK) return rc;
-    }
     m->conc_var = v;
+    m->fixed[2] = ts != 0;
     return PYJAC_OK;
   }
   const bool jac = which == 1;
@@ -539,15 +586,12 @@ pyjac_status pyjac_mech_set_variant(pyjac_mech* m, int32_t which, int32_t ts, in
     if (ts <= 0 || nt <= 0 || nt % ts) return fail(PYJAC_E_INVALID, "bad variant");
     if (kpt_of(m->host.N, ts, nt) > 8 || tile_lds_bytes(m->host.N, m->host.NR, m->host.NG, ts, nt, jac) > m->max_lds)
       return fail(PYJAC_E_UNSUPPORTED, "variant does not fit");
-    static const int ok[][2] = {{16, 512}, {16, 1024}, {8, 512}, {8, 1024}, {4, 512}, {4, 1024},
-                                {2, 512},  {2, 1024}, {32, 1024}, {64, 1024}, {8, 256}, {4, 256}};
     bool found = false;
-    for (auto& q : ok) found |= (q[0] == ts && q[1] == nt);
+    for (auto& q : kShapes) found |= (q[0] == ts && q[1] == nt);
     if (!found) return fail(PYJAC_E_UNSUPPORTED, "variant not compiled");
   }
-  pyjac_status rc = ensure_var(m, v, jac);
-  if (rc != PYJAC_OK) return rc;
   (jac ? m->jac_var : m->rates_var) = v;
+  m->fixed[which] = ts != 0;
   return PYJAC_OK;
 }
 
@@ -563,8 +607,6 @@ pyjac_status pyjac_mech_autotune(pyjac_mech* m, int32_t which, int64_t n, int64_
   if (n_entries) *n_entries = 0;
   const bool jac = which == 1;
   const hipStream_t st = static_cast<hipStream_t>(stream);
-  static const int shapes_all[][2] = {{16, 1024}, {16, 512}, {32, 1024}, {64, 1024}, {8, 512}, {8, 1024},
-                                      {4, 512},   {4, 1024}, {2, 512},   {2, 1024},  {8, 256}, {4, 256}};
   int prev = 0;
   hipGetDevice(&prev);
   hipSetDevice(m->device);
@@ -580,15 +622,14 @@ pyjac_status pyjac_mech_autotune(pyjac_mech* m, int32_t which, int64_t n, int64_
   rc = PYJAC_OK;
   const bool conc = which == 2;
   const int n_shapes = conc ? (int)(sizeof(kConcShapes) / sizeof(kConcShapes[0]))
-                            : (int)(sizeof(shapes_all) / sizeof(shapes_all[0]));
+                            : (int)(sizeof(kShapes) / sizeof(kShapes[0]));
   for (int si = 0; si < n_shapes; ++si) {
     const Variant v = conc ? Variant{kConcShapes[si][0], kConcShapes[si][1]}
-                           : Variant{shapes_all[si][0], shapes_all[si][1]};
+                           : Variant{kShapes[si][0], kShapes[si][1]};
     if (kpt_of(m->host.N, v.ts, v.nt) > 8) continue;
     const size_t lds = kind_lds(m, which, v);
     if (lds > m->max_lds) continue;
-    if ((rc = ensure_var(m, v, jac || conc)) != PYJAC_OK) break;
-    const MechDev md = launch_view(m, v, jac || conc);
+    const MechDev md = launch_view(m, v);
     auto launch = [&]() {
       if (conc) return launch_conc(v.ts, v.nt, md, n, ld, phi, out, lds, st);
       return jac ? launch_tile(true, v.ts, v.nt, md, n, ld, phi, p, nullptr, nullptr, nullptr, nullptr,
@@ -629,6 +670,7 @@ pyjac_status pyjac_mech_autotune(pyjac_mech* m, int32_t which, int64_t n, int64_
   if (rc != PYJAC_OK) return rc;
   if (!best.ts) return fail(PYJAC_E_UNSUPPORTED, "no launch shape fits");
   (conc ? m->conc_var : jac ? m->jac_var : m->rates_var) = best;
+  m->fixed[which] = true;
   if (n_entries) *n_entries = count < max_entries ? count : max_entries;
   return PYJAC_OK;
 }
