@@ -6,8 +6,8 @@
 //              matrix per state (FP64 or FP32), through an LDS tile so both
 //              the reads and the writes are coalesced.
 //  lu, solve : newton_blocked.hip.
-//  residual  : r = b - (I - h gamma J) x in FP64, one thread per state,
-//              straight from the state-fastest Jacobian (coalesced).
+//  residual  : r = b - (I - h gamma J) x in FP64, straight from the
+//              state-fastest Jacobian (coalesced).
 // Mode 1 (mixed) factors in FP32, refines in FP64 and re-solves the states
 // that do not converge with the FP64 path (compacted list, device-side).
 // Systems with N <= 64 take register-resident kernels instead (FP64: one
@@ -44,6 +44,7 @@ __global__ __launch_bounds__(256) void form_kernel(int N, int64_t n, int64_t ld,
   const int64_t e0 = (int64_t)blockIdx.y * 64;
   const int64_t s0 = (int64_t)blockIdx.x * 16;
   const int64_t lim = count ? *count : n;
+  if (s0 >= lim) return;               // a listed launch is sized for every state
   // load: lanes state-fastest
   {
     const int s = tid % 16;
@@ -790,44 +791,55 @@ hipError_t launch_small(int N, int64_t n, int64_t ld, const double* jac, const d
   return hipErrorInvalidValue;
 }
 
-// r = b - (I - h gamma J) x in FP64.  grid (ceil(n / 256), ceil(N / 8)): one
-// thread per (state, block of 8 rows), so that a few thousand states still
-// fill the device; each x_j load serves 8 multiply-adds and every load is
-// coalesced across the states of a wavefront.  Converged states are skipped.
-constexpr int kResRows = 8;
+// r = b - (I - h gamma J) x in FP64.  grid (ceil(n / 32), ceil(N / 8)): a
+// workgroup forms eight rows of 32 states, its threads one column in eight of
+// one state each; the eight partial sums of a row are added in a fixed order.
+// Each x_j load serves 8 multiply-adds, and 32 states are a 256-byte run.  One
+// thread per (state, 8 rows) left a few hundred states with too few wavefronts
+// and a chain of N loads: 410 us a sweep for 256 states of 360 species.
+// Converged states are skipped.
+constexpr int kResRows = 8, kResStates = 32;
 __global__ __launch_bounds__(256) void residual_kernel(int N, int64_t n, int64_t ld, const double* __restrict__ jac,
                                                        const double* __restrict__ h, double gamma,
                                                        const double* __restrict__ rhs, const double* __restrict__ xs,
                                                        double* __restrict__ rbuf, const int* __restrict__ status) {
-  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= n || status[s] != ST_UNSET) return;
-  const double hg = h[s] * gamma;
-  constexpr int IB = kResRows;
-  {
-    const int i0 = blockIdx.y * IB;
-    double acc[IB];
+  constexpr int IB = kResRows, NS = kResStates, NJ = 256 / kResStates;
+  static_assert(IB == NJ, "a thread finishes one row of its state");
+  __shared__ double part[IB][NJ][NS + 1];
+  const int sl = threadIdx.x % NS, jl = threadIdx.x / NS;
+  const int64_t s = (int64_t)blockIdx.x * NS + sl;
+  const bool act = s < n && status[s] == ST_UNSET;
+  if (!__syncthreads_or(act)) return;
+  const int i0 = blockIdx.y * IB;
+  double acc[IB];
 #pragma unroll
-    for (int u = 0; u < IB; ++u) acc[u] = 0.0;
-    for (int j = 0; j < N; ++j) {
+  for (int u = 0; u < IB; ++u) acc[u] = 0.0;
+  if (act) {
+    const double* jp = jac + (int64_t)i0 * N * ld + s;
+    const int64_t rs = (int64_t)N * ld;
+    const int rows = min(IB, N - i0);
+#pragma unroll 2
+    for (int j = jl; j < N; j += NJ) {
       const double xj = xs[(int64_t)j * n + s];
 #pragma unroll
-      for (int u = 0; u < IB; ++u)
-        if (i0 + u < N) acc[u] += jac[((int64_t)(i0 + u) * N + j) * ld + s] * xj;
+      for (int u = 0; u < IB; ++u) acc[u] += jp[min(u, rows - 1) * rs + (int64_t)j * ld] * xj;
     }
+  }
 #pragma unroll
-    for (int u = 0; u < IB; ++u) {
-      const int i = i0 + u;
-      if (i < N) rbuf[(int64_t)i * n + s] = rhs[(int64_t)i * ld + s] - (xs[(int64_t)i * n + s] - hg * acc[u]);
-    }
+  for (int u = 0; u < IB; ++u) part[u][jl][sl] = acc[u];
+  __syncthreads();
+  const int i = i0 + jl;
+  if (act && i < N) {
+    double a = part[jl][0][sl];
+#pragma unroll
+    for (int q = 1; q < NJ; ++q) a += part[jl][q][sl];
+    rbuf[(int64_t)i * n + s] = rhs[(int64_t)i * ld + s] - (xs[(int64_t)i * n + s] - h[s] * gamma * a);
   }
 }
 
-__global__ void init_status_kernel(int64_t n, int* __restrict__ status, double* __restrict__ xs, int N) {
+__global__ void init_status_kernel(int64_t n, int* __restrict__ status) {
   const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= n) return;
-  status[s] = ST_UNSET;
-  if (xs)
-    for (int i = 0; i < N; ++i) xs[(int64_t)i * n + s] = 0.0;
+  if (s < n) status[s] = ST_UNSET;
 }
 
 // dst[s] = src[s]: keeps the status left by a factorization (singular
@@ -835,12 +847,6 @@ __global__ void init_status_kernel(int64_t n, int* __restrict__ status, double* 
 __global__ void copy_status_kernel(int64_t n, const int* __restrict__ src, int* __restrict__ dst) {
   const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (s < n) dst[s] = src[s];
-}
-
-__global__ void copy_rhs_kernel(int N, int64_t n, int64_t ld, const double* __restrict__ rhs, double* __restrict__ rbuf) {
-  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= n) return;
-  for (int i = 0; i < N; ++i) rbuf[(int64_t)i * n + s] = rhs[(int64_t)i * ld + s];
 }
 
 // States that did not converge (status still unset) go to the FP64 list.
@@ -855,20 +861,15 @@ __global__ void compact_kernel(int64_t n, const int* __restrict__ status, int* _
   }
 }
 
-__global__ void finish_kernel(int N, int64_t n, int64_t ld, const int* __restrict__ status,
-                              const double* __restrict__ xs, double* __restrict__ xout, int* __restrict__ info,
+__global__ void finish_kernel(int64_t n, const int* __restrict__ status, int* __restrict__ info,
                               const int* __restrict__ fb_status, int mode) {
   const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= n) return;
   int st = status[s];
-  if (mode == 1) {
-    if (st >= 0 && xs)
-      for (int i = 0; i < N; ++i) xout[(int64_t)i * ld + s] = xs[(int64_t)i * n + s];
-    if (st == ST_UNSET || st == ST_SING32) st = (fb_status[s] == 0) ? -2 : fb_status[s];   // FP64 re-solve
-  }
+  if (mode == 1 && (st == ST_UNSET || st == ST_SING32))
+    st = (fb_status[s] == 0) ? -2 : fb_status[s];      // FP64 re-solve
   info[s] = st;
 }
-
 
 size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 size_t small_ws_bytes(int64_t n, int mode) { return mode == 1 ? align256((size_t)n * sizeof(int)) + 256 : 0; }
@@ -1054,11 +1055,10 @@ pyjac_status pyjac_newton_factor_solve(const pyjac_mech* m, int64_t n, int64_t l
     if (reuse)
       hipLaunchKernelGGL(copy_status_kernel, dim3(g1), dim3(256), 0, st, n, (const int*)sing, status);
     else
-      hipLaunchKernelGGL(init_status_kernel, dim3(g1), dim3(256), 0, st, n, status, (double*)nullptr, N);
+      hipLaunchKernelGGL(init_status_kernel, dim3(g1), dim3(256), 0, st, n, status);
     e = run_direct<double>(N, n, ld, jac, h, gamma, rhs, x, A64, piv, nullptr, nullptr, status, st, !reuse, sing);
     if (e == hipSuccess) {
-      hipLaunchKernelGGL(finish_kernel, dim3(g1), dim3(256), 0, st, N, n, ld, (const int*)status, (const double*)nullptr,
-                         x, info, (const int*)nullptr, 0);
+      hipLaunchKernelGGL(finish_kernel, dim3(g1), dim3(256), 0, st, n, (const int*)status, info, (const int*)nullptr, 0);
       e = hipGetLastError();
     }
   } else {
@@ -1068,10 +1068,10 @@ pyjac_status pyjac_newton_factor_solve(const pyjac_mech* m, int64_t n, int64_t l
     int* list = reinterpret_cast<int*>(w + L.list);
     int* count = reinterpret_cast<int*>(w + L.count);
     double* dprev = reinterpret_cast<double*>(w + L.dprev);
-    hipLaunchKernelGGL(init_status_kernel, dim3(g1), dim3(256), 0, st, n, status, xs, N);
-    if (reuse) hipLaunchKernelGGL(copy_status_kernel, dim3(g1), dim3(256), 0, st, n, (const int*)sing, status);
-    hipLaunchKernelGGL(copy_rhs_kernel, dim3(g1), dim3(256), 0, st, N, n, ld, rhs, rbuf);
-    if (!reuse) {
+    if (reuse) {
+      hipLaunchKernelGGL(copy_status_kernel, dim3(g1), dim3(256), 0, st, n, (const int*)sing, status);
+    } else {
+      hipLaunchKernelGGL(init_status_kernel, dim3(g1), dim3(256), 0, st, n, status);
       dim3 fg((unsigned)((n + 15) / 16), (unsigned)(((int64_t)N * N + 63) / 64));
       hipLaunchKernelGGL(form_kernel<float>, fg, dim3(256), 0, st, N, n, ld, jac, h, gamma, A32, (const int*)nullptr,
                          (const int*)nullptr, status);
@@ -1081,21 +1081,20 @@ pyjac_status pyjac_newton_factor_solve(const pyjac_mech* m, int64_t n, int64_t l
     }
     for (int sweep = 0; sweep <= max_refine; ++sweep) {
       if (sweep > 0)
-        hipLaunchKernelGGL(residual_kernel, dim3(g1, (unsigned)((N + kResRows - 1) / kResRows)), dim3(256), 0, st, N,
-                           n, ld, jac, h, gamma, rhs, (const double*)xs,
-                           rbuf, (const int*)status);
-      e = launch_solve_refine(N, n, A32, piv, rbuf, xs, status, sweep, rtol, dprev, st);
+        hipLaunchKernelGGL(residual_kernel,
+                           dim3((unsigned)((n + kResStates - 1) / kResStates), (unsigned)((N + kResRows - 1) / kResRows)),
+                           dim3(256), 0, st, N, n, ld, jac, h, gamma, rhs, (const double*)xs, rbuf, (const int*)status);
+      e = launch_solve_refine(N, n, ld, A32, piv, rhs, rbuf, xs, x, status, sweep, rtol, dprev, st);
       if (e != hipSuccess) return fail(PYJAC_E_DEVICE, hipGetErrorString(e));
     }
     // FP64 re-solve of the states that did not converge (or whose FP32 factor was singular)
     hipLaunchKernelGGL(zero_int_kernel, dim3(1), dim3(1), 0, st, count);
     hipLaunchKernelGGL(compact_kernel, dim3(g1), dim3(256), 0, st, n, (const int*)status, list, count);
-    hipLaunchKernelGGL(init_status_kernel, dim3(g1), dim3(256), 0, st, n, fbs, (double*)nullptr, N);
+    hipLaunchKernelGGL(init_status_kernel, dim3(g1), dim3(256), 0, st, n, fbs);
     // (always factored: which states fall back depends on the right-hand side)
     e = run_direct<double>(N, n, ld, jac, h, gamma, rhs, x, A64, piv64, list, count, fbs, st);
     if (e == hipSuccess) {
-      hipLaunchKernelGGL(finish_kernel, dim3(g1), dim3(256), 0, st, N, n, ld, (const int*)status, (const double*)xs, x,
-                         info, (const int*)fbs, 1);
+      hipLaunchKernelGGL(finish_kernel, dim3(g1), dim3(256), 0, st, n, (const int*)status, info, (const int*)fbs, 1);
       e = hipGetLastError();
     }
   }

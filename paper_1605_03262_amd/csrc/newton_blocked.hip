@@ -298,6 +298,7 @@ __global__ __launch_bounds__(256, R * sizeof(T) <= 16 ? 3 : 2) void solve_kernel
                                                     double* __restrict__ xout, const int* __restrict__ list,
                                                     const int* __restrict__ count, int* __restrict__ status,
                                                     int sweep, double rtol, double* __restrict__ dprev) {
+  const bool first = !REFINE || sweep == 0;           // right-hand side as given
   constexpr int CB = R * sizeof(T) <= 16 ? 8 : R * sizeof(T) <= 48 ? 4 : 2;
   const int lane = threadIdx.x % 64, wv = threadIdx.x / 64;
   const int64_t slot = (int64_t)blockIdx.x * 4 + wv;
@@ -315,7 +316,7 @@ __global__ __launch_bounds__(256, R * sizeof(T) <= 16 ? 3 : 2) void solve_kernel
     dg[i] = T(1);
     if (r < N) {
       const int64_t row = piv[r];
-      b[i] = REFINE ? (T)rbuf[row * n + st] : (T)rhs[row * ld + st];
+      b[i] = first ? (T)rhs[row * ld + st] : (T)rbuf[row * n + st];
       dg[i] = A[(int64_t)r * N + r];
     }
     rd[i] = T(1) / dg[i];
@@ -395,32 +396,40 @@ __global__ __launch_bounds__(256, R * sizeof(T) <= 16 ? 3 : 2) void solve_kernel
     if (lane == 0 && s0 == ST_UNSET) status[st] = fin ? 0 : -1;
     return;
   }
-  double dmax = 0.0, xmax = 0.0;
+  double dmax = 0.0, xmax = 0.0, xv[R];
   sfor<0, R>([&](auto i) {
     const int r = lane + 64 * i;
+    xv[i] = 0.0;
     if (r < N) {
       const double d = (double)b[i];
-      const double xv = xs[(int64_t)r * n + st] + d;
-      xs[(int64_t)r * n + st] = xv;
+      xv[i] = first ? d : xs[(int64_t)r * n + st] + d;
+      xs[(int64_t)r * n + st] = xv[i];
       dmax = fmax(dmax, fabs(d));
-      xmax = fmax(xmax, fabs(xv));
-      fin = fin && isfinite(xv);
+      xmax = fmax(xmax, fabs(xv[i]));
+      fin = fin && isfinite(xv[i]);
     }
   });
+  if (first) return;
   for (int o = 32; o > 0; o >>= 1) {
     dmax = fmax(dmax, __shfl_xor(dmax, o));
     xmax = fmax(xmax, __shfl_xor(xmax, o));
   }
   fin = __all(fin);
-  if (lane == 0 && sweep > 0) {
-    // converged when the correction is below rtol of the solution, or when
-    // the contraction rho of the last two corrections (refinement converges
-    // linearly) predicts the remaining error rho / (1 - rho) |d| below it
-    const double dp = sweep >= 2 ? dprev[st] : 0.0;
-    const double rho = dp > 0.0 ? dmax / dp : 1.0;
-    if (fin && (dmax <= rtol * xmax || (rho < 0.5 && rho * dmax <= rtol * xmax * (1.0 - rho)))) status[st] = sweep;
+  // converged when the correction is below rtol of the solution, or when
+  // the contraction rho of the last two corrections (refinement converges
+  // linearly) predicts the remaining error rho / (1 - rho) |d| below it
+  const double dp = sweep >= 2 ? dprev[st] : 0.0;
+  const double rho = dp > 0.0 ? dmax / dp : 1.0;
+  const bool conv = fin && (dmax <= rtol * xmax || (rho < 0.5 && rho * dmax <= rtol * xmax * (1.0 - rho)));
+  if (lane == 0) {
+    if (conv) status[st] = sweep;
     dprev[st] = dmax;
   }
+  if (conv)
+    sfor<0, R>([&](auto i) {
+      const int r = lane + 64 * i;
+      if (r < N) xout[(int64_t)r * ld + st] = xv[i];
+    });
 }
 
 template <typename T, int NT, int NB>
@@ -476,10 +485,11 @@ hipError_t launch_solve_direct(int N, int64_t n, int64_t ld, const T* A, const i
 template hipError_t launch_solve_direct<double>(int, int64_t, int64_t, const double*, const int*, const double*,
                                                 double*, const int*, const int*, int*, hipStream_t);
 
-hipError_t launch_solve_refine(int N, int64_t n, const float* A, const int* piv, const double* rbuf, double* xs,
-                               int* status, int sweep, double rtol, double* dprev, hipStream_t st) {
-  return launch_solve<float, true>(N, n, n, A, piv, nullptr, rbuf, xs, nullptr, nullptr, nullptr, status, sweep, rtol,
-                                   dprev, st);
+hipError_t launch_solve_refine(int N, int64_t n, int64_t ld, const float* A, const int* piv, const double* rhs,
+                               const double* rbuf, double* xs, double* xout, int* status, int sweep, double rtol,
+                               double* dprev, hipStream_t st) {
+  return launch_solve<float, true>(N, n, ld, A, piv, rhs, rbuf, xs, xout, nullptr, nullptr, status, sweep, rtol, dprev,
+                                   st);
 }
 
 }  // namespace pyjac

@@ -28,9 +28,11 @@ hipError_t launch_lu(int N, int64_t n, T* A, int* piv, const int* list, const in
 template <typename T>
 hipError_t launch_solve_direct(int N, int64_t n, int64_t ld, const T* A, const int* piv, const double* rhs,
                                double* xout, const int* list, const int* count, int* status, hipStream_t st);
-// refine: d = A^-1 r with r from rbuf [N][n]; x += d in xs [N][n] (FP64); the
-// state converges at this sweep by the tests of the kernel.
-hipError_t launch_solve_refine(int N, int64_t n, const float* A, const int* piv, const double* rbuf, double* xs,
-                               int* status, int sweep, double rtol, double* dprev, hipStream_t st);
+// refine: sweep 0 x = A^-1 b into xs [N][n] (FP64); later sweeps d = A^-1 r
+// with r from rbuf [N][n] and x += d; a state that converges by the tests of
+// the kernel gets status = sweep and its x in xout [N][ld].
+hipError_t launch_solve_refine(int N, int64_t n, int64_t ld, const float* A, const int* piv, const double* rhs,
+                               const double* rbuf, double* xs, double* xout, int* status, int sweep, double rtol,
+                               double* dprev, hipStream_t st);
 
 }  // namespace pyjac
