@@ -76,3 +76,27 @@ def test_largest_size():
     with pytest.raises(PyjacError, match="too large"):
         M.newton_solve(d(J), d(h), d(b), GAMMA, mode=0)
     torch.cuda.synchronize()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("mode,exps", [(0, [-1010, 0, 1005]), (1, [-122, 0, 121])])
+@pytest.mark.parametrize("N", [65, 129, 513])
+def test_pivots_at_the_ends_of_the_range(N, mode, exps):
+    # A = 2^e B with a zero diagonal in B, exact in J (h gamma = 1); the
+    # solution is that of B, the bar 100 kappa u as above
+    import torch
+    from paper_1605_03262_amd import Mechanism
+    rng = np.random.default_rng(N)
+    B = rng.standard_normal((N, N))
+    np.fill_diagonal(B, 0.0)
+    b = rng.standard_normal(N)
+    xr, kappa = np.linalg.solve(B, b), np.linalg.cond(B, np.inf)
+    J = np.stack([np.eye(N) - 2.0 ** e * B for e in exps], axis=-1)    # B's diagonal is zero: exact
+    rhs = np.stack([2.0 ** e * b for e in exps], axis=-1)
+    M = Mechanism(text=isomer_mechanism(N))
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    x, info = M.newton_solve(d(J.reshape(N * N, -1)), d(np.full(len(exps), 2.0)), d(rhs), GAMMA, mode=mode)
+    x, info = x.cpu().numpy(), info.cpu().numpy()
+    assert np.all((info >= 0) | (info == -2)), info
+    err = np.max(np.abs(x - xr[:, None]), axis=0) / np.max(np.abs(xr))
+    assert np.all(err <= 100 * kappa * U), err / (kappa * U)
