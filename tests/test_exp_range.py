@@ -1,0 +1,100 @@
+"""The rate coefficients' exponentials over their whole range: blending terms
+switched off by extreme parameters (exponents down to -1e103, where exp is 0),
+rate coefficients whose exponent is as large, and exponents up to the ends of
+the double range.  Rates, Jacobian and concentration form against the oracle,
+with the bars of the other parity tests.
+"""
+import numpy as np
+import pytest
+
+from conftest import tiny
+from synth import draw_states
+from test_gpu_conc import densify, gpu_conc
+from test_gpu_parity import JAC_TOL, RATE_TOL, check_jac, check_rates, enorm_per_state, gpu_jac, gpu_mech, gpu_rates
+from test_oracle_conc_pins import conc_states
+
+pytestmark = pytest.mark.gpu
+
+# (a, T***, T*[, T**]) and (a, b, c): a term off by a tiny or a huge parameter
+TROE = [(0.6, 1e-30, 300.0), (0.6, 1e-50, 300.0), (0.6, 1e-100, 300.0), (0.6, 100.0, 1e-42), (0.6, 100.0, 1e-100),
+        (0.6, 100.0, 300.0, 1e30), (0.6, 100.0, 300.0, 1e50), (0.6, 100.0, 300.0, 1e100),
+        (0.6, 1e100, 1e-100, 1e100), (0.6, 1e100, 1e100, 1e-100)]
+SRI = [(0.5, 100.0, 1e-30), (0.5, 100.0, 1e-50), (0.5, 100.0, 1e-100), (0.5, 1e50, 500.0), (0.5, 1e100, 500.0),
+       (0.5, 1e-100, 1e100)]
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+    return t
+
+
+def parity(torch, mech, label):
+    from oracle import RefMech
+    ref, M = RefMech(text=mech.to_text()), gpu_mech(mech)
+    phi, p = draw_states(77, mech.n_species, 37, T=(700.0, 2400.0), P_atm=(0.3, 80.0), dirichlet=0.5)
+    check_rates(gpu_rates(torch, M, phi, p, ld=41), ref.eval_rates(phi, p), mech, phi, p, label)
+    check_jac(gpu_jac(torch, M, phi, p, ld=41), ref.eval_jacobian(phi, p), label)
+    c = conc_states(mech, phi, p)
+    out, (colptr, rowidx) = gpu_conc(torch, M, c), M.conc_pattern()
+    assert np.all(np.isfinite(out)), label
+    e = enorm_per_state(densify(out, colptr, rowidx, mech.n_species), ref.eval_jacobian_conc(c))
+    assert e.max() <= JAC_TOL, (label, e.max())
+
+
+@pytest.mark.parametrize("kind", ["falloff_troe", "chemact_troe", "falloff_sri", "chemact_sri"])
+def test_blending_terms_off(torch, oracle_built, kind):
+    mech = tiny(31, {kind: 1, "elementary": 2}, collider_probs=(0.5, 0.0))
+    r = next(q for q in mech.reactions if q.kind == kind)
+    for par in TROE if "troe" in kind else SRI:
+        if "troe" in kind:
+            r.troe = par
+        else:
+            r.sri = par
+        parity(torch, mech, f"{kind} {par}")
+
+
+@pytest.mark.parametrize("kind,ta", [("elementary", 1e45), ("elementary", 1e50), ("elementary", 1e100),
+                                     ("plog", 1e50), ("plog", 1e100), ("explicit", 1e50), ("explicit", 1e100)])
+def test_rate_coefficient_off(torch, oracle_built, kind, ta):
+    # a second, ordinary reaction keeps the state's scale
+    first = "plog" if kind == "plog" else "elementary"
+    mech = tiny(32, {"plog": 1, "elementary": 2}, rev_mix={"explicit" if kind == "explicit" else "irrev": 1.0})
+    r = next(q for q in mech.reactions if q.kind == first)
+    if kind == "plog":
+        r.plog = [(q[0], q[1], q[2], ta) for q in r.plog]
+    elif kind == "explicit":
+        r.reverse = (r.reverse[0], r.reverse[1], ta)
+    else:
+        r.arr = (r.arr[0], r.arr[1], ta)
+    parity(torch, mech, f"{kind} {ta}")
+
+
+def ladder_mechanism(ta):
+    out = ["pyjac-mech 1", "elements 1", "  H 1.008", "species 2"]
+    for k in range(2):
+        out += [f"  S{k} 2.016 1000.0 1 H 2"] + ["    2.5 0.0 0.0 0.0 0.0 100.0 1.0"] * 2
+    out += [f"reactions {len(ta)}"]
+    for t in ta:
+        out += ["reaction elementary irrev", "reactants 1 S0 1", "products 1 S1 1", f"arrhenius 1.0 0.0 {t!r}"]
+    return "\n".join(out + ["end"]) + "\n"
+
+
+def test_exponents_to_the_ends_of_the_range(torch, oracle_built):
+    """k_f = exp(-Ta / T) at exponents from -705 to 705, and past them, where the
+    result is 0 or inf; a NaN temperature stays one."""
+    from oracle import RefMech
+    from paper_1605_03262_amd import Mechanism
+    ends = [1e3, 1e6, 1e10, 1e16, 1e20, 1e45, 1e46, 1e60, 1e100, 1e300]
+    T0 = 1024.0
+    ta = list(np.linspace(-705.0, 705.0, 283) * T0) + [e * T0 for e in ends] + [-e * T0 for e in ends]
+    text = ladder_mechanism([float(t) for t in ta])
+    phi = np.array([[T0, 0.999 * T0, 1.001 * T0, np.nan], [0.5, 0.25, 1.0, 0.5]])
+    p = np.full(4, 101325.0)
+    r, ref = Mechanism(text=text).eval_rates(torch.from_numpy(phi).cuda(), torch.from_numpy(p).cuda()), RefMech(text=text)
+    g, o = r["rop_f"].cpu().numpy(), ref.eval_rates(phi[:, :3].copy(), p[:3].copy())["rop_f"]
+    n = 283
+    assert np.all(np.isnan(g[:, 3]))
+    assert np.all(np.abs(g[:n, :3] - o[:n]) <= RATE_TOL * np.abs(o[:n]))
+    assert np.all(g[n:n + len(ends), :3] == 0.0) and np.all(o[n:n + len(ends)] == 0.0)
+    assert np.all(g[n + len(ends):, :3] == np.inf) and np.all(o[n + len(ends):] == np.inf)
