@@ -46,10 +46,26 @@ __device__ __forceinline__ void sfor(F&& f) {
   }
 }
 
-__device__ __forceinline__ unsigned mag_key(double v) {
-  return (unsigned)((unsigned long long)__double_as_longlong(v) >> 32) & 0x7FFFFFFFu;
+// The bits of |v|, which order as the magnitudes do.
+__device__ __forceinline__ unsigned long long mag_key(double v) {
+  return (unsigned long long)__double_as_longlong(v) & 0x7FFFFFFFFFFFFFFFull;
 }
 __device__ __forceinline__ unsigned mag_key(float v) { return (unsigned)__float_as_int(v) & 0x7FFFFFFFu; }
+
+// The first lane that holds the wavefront's largest key; of 64-bit keys the low
+// halves are looked at where several lanes share the largest high half.
+__device__ __forceinline__ int first_max(unsigned key) {
+  return (int)__builtin_ctzll(__ballot(key == __ockl_wfred_max_u32(key)));
+}
+__device__ __forceinline__ int first_max(unsigned long long key) {
+  const unsigned hi = (unsigned)(key >> 32), mh = __ockl_wfred_max_u32(hi);
+  unsigned long long m = __ballot(hi == mh);
+  if (m & (m - 1)) {
+    const unsigned lo = hi == mh ? (unsigned)key : 0u, ml = __ockl_wfred_max_u32(lo);
+    m = __ballot(hi == mh && lo == ml);
+  }
+  return (int)__builtin_ctzll(m);
+}
 
 __device__ __forceinline__ double read_lane(double v, int lane) {
   const unsigned long long u = __double_as_longlong(v);
@@ -65,12 +81,11 @@ __device__ __forceinline__ float read_lane(float v, int lane) {
 // Right-looking LU with partial pivoting in panels of NB columns; thread t is
 // row position t (N <= NT).
 //  1. Panel: every thread keeps its row of the panel in registers.  One step
-//     per column: the largest |a| of each wavefront (compared on the high 32
-//     bits of the FP64 pattern or the FP32 pattern, which order non-negative
-//     values) enters an LDS maximum; after a barrier the winner's row, with
-//     the reciprocal of its pivot (every thread has computed its own
-//     meanwhile), goes through LDS to all threads, which eliminate.  Rows are
-//     not exchanged meanwhile.
+//     per column: the largest |a| of each wavefront goes to LDS; after a
+//     barrier every wavefront sees whether its own is the largest (the first
+//     of equal ones), and the winner's row, with the reciprocal of its pivot
+//     (every thread has computed its own meanwhile), goes through LDS to all
+//     threads, which eliminate.  Rows are not exchanged meanwhile.
 //  2. The pivot rows move to the top of the panel and the rows they displace
 //     to the places left.  In the columns to the right this is done with the
 //     reads for U12; in the columns to the left it is put off to the end,
@@ -106,7 +121,7 @@ constexpr int lu_waves() { return NT >= 1024 ? 4 : CW <= 64 ? 3 : sizeof(T) == 8
 template <typename T, int NT, int NB, int CW>
 size_t lu_lds(int N) {
   const size_t panels = (N + NB - 1) / NB;
-  return ((lu_cols(N, NB, CW) + 1) * lu_ps<T>(NB) + NB * NB) * sizeof(T) + 3 * sizeof(unsigned long long) +
+  return ((lu_cols(N, NB, CW) + 1) * lu_ps<T>(NB) + NB * NB) * sizeof(T) + NT / 64 * sizeof(unsigned long long) +
          (5 * NB + NT + 1) * sizeof(int) + panels * N * sizeof(unsigned short);
 }
 
@@ -155,8 +170,10 @@ __global__ __launch_bounds__(NT, (lu_waves<T, NT, CW>())) void lu_kernel(int N, 
   T* Us = reinterpret_cast<T*>(smem);           // [uc][PS]: U12, column by column
   T* Lt = Us + (size_t)uc * PS;                 // [NB][NB]: L11 transposed
   T* prow = Lt + NB * NB;                       // [PS]: pivot row, 1 / pivot at [NB]
-  unsigned long long* win = reinterpret_cast<unsigned long long*>(prow + PS);   // [3] largest key and its row, in turn
-  int* pvp = reinterpret_cast<int*>(win + 3);   // [NB] row position of each pivot of the panel
+  typedef decltype(mag_key(T())) key_t;
+  unsigned long long* keys = reinterpret_cast<unsigned long long*>(prow + PS);
+  key_t* wkey = reinterpret_cast<key_t*>(keys); // [NW] largest key of each wavefront
+  int* pvp = reinterpret_cast<int*>(keys + NW); // [NB] row position of each pivot of the panel
   int* dl = pvp + NB;                           // displaced rows' positions ...
   int* vl = dl + NB;                            // ... and where they go
   int* newp = vl + NB;                          // [NB] the same by position in the panel
@@ -164,10 +181,8 @@ __global__ __launch_bounds__(NT, (lu_waves<T, NT, CW>())) void lu_kernel(int N, 
   int* prm = taken + NB;                        // [NT] matrix row at each position
   int* nmv = prm + NT;                          // number of displaced rows
   unsigned short* smap = reinterpret_cast<unsigned short*>(nmv + 1);   // [panels][N] position before the panel's exchange
-  int orig = t, ws = 0;
+  int orig = t;
   bool sing = false;
-  if (t < 3) win[t] = 0;
-  __syncthreads();
   for (int k0 = 0; k0 < N; k0 += NB) {
     const int nb = min(NB, N - k0), W = N - k0 - nb, o = k0 + NB;
     const bool inp = t >= k0 && t < N;
@@ -180,24 +195,22 @@ __global__ __launch_bounds__(NT, (lu_waves<T, NT, CW>())) void lu_kernel(int N, 
     }
     sfor<0, NB>([&](auto c) {
       if (c < nb) {
-        const unsigned key = act ? mag_key(a[c]) + 1u : 0u;
+        const key_t key = act ? mag_key(a[c]) + 1u : key_t(0);
         const T rc = recip(a[c]);
-        const unsigned mk = __ockl_wfred_max_u32(key);
-        const bool first = lane == (int)__builtin_ctzll(__ballot(key == mk));
-        const unsigned long long me = ((unsigned long long)mk << 32) | (unsigned)(0xFFFF - t);
-        if (first) atomicMax(win + ws, me);
-        if (t == 0) win[ws == 2 ? 0 : ws + 1] = 0;
+        const bool first = lane == first_max(key);
+        if (first) wkey[wave] = key;
         __syncthreads();
-        const int pr = 0xFFFF - (int)(win[ws] & 0xFFFFu);
-        ws = ws == 2 ? 0 : ws + 1;
-        if (t == pr) {
+        const int w = min(lane, NW - 1);
+        const key_t mine = wkey[wave], other = wkey[w];
+        const bool me = __ballot(other > mine || (other == mine && w < wave)) == 0 && first;
+        if (me) {
           sfor<decltype(c)::value, NB>([&](auto j) { prow[j] = a[j]; });
           prow[NB] = rc;
         }
         __syncthreads();
         const T inv = prow[NB];
         sing = sing || !(fabs(prow[c]) > T(0));
-        if (t == pr) {
+        if (me) {
           act = false;
           step = c;
         }
