@@ -387,6 +387,7 @@ __global__ __launch_bounds__(256, R * sizeof(T) <= 16 ? 3 : 2) void solve_kernel
   const T* A = Aall + slot * (int64_t)N * N;
   const int* piv = pivall + slot * (int64_t)N;
   T b[R], rd[R], dg[R];
+  bool rdok = true;
   sfor<0, R>([&](auto i) {
     const int r = lane + 64 * i;
     b[i] = T(0);
@@ -397,6 +398,7 @@ __global__ __launch_bounds__(256, R * sizeof(T) <= 16 ? 3 : 2) void solve_kernel
       dg[i] = A[(int64_t)r * N + r];
     }
     rd[i] = T(1) / dg[i];
+    rdok = rdok && isfinite(rd[i]);
   });
   // forward: unit lower
   sfor<0, R>([&](auto S) {
@@ -426,8 +428,20 @@ __global__ __launch_bounds__(256, R * sizeof(T) <= 16 ? 3 : 2) void solve_kernel
       apply(buf[1], kb + CB);
     }
   });
-  // backward: upper
-  sfor<0, R>([&](auto S) {
+  // backward: upper.  A pivot whose reciprocal is not finite (below 2^-1024, in
+  // FP32 2^-128) is divided by, in a plain loop.
+  if (!__all(rdok)) sfor<0, R>([&](auto S) {
+    constexpr int s = R - 1 - decltype(S)::value;
+    for (int kk = min(64, N - 64 * s) - 1; kk >= 0; --kk) {
+      const T* col = A + (int64_t)(64 * s + kk) * N + lane;
+      const T x = b[s] / dg[s], xk = read_lane(x, kk);
+      if (lane == kk) b[s] = x;
+      sfor<0, s + 1>([&](auto i) {
+        if (i < s || lane < kk) b[i] = fma(-col[64 * i], xk, b[i]);
+      });
+    }
+  });
+  else sfor<0, R>([&](auto S) {
     constexpr int s = R - 1 - decltype(S)::value, RS = s + 1;
     const int nk = min(64, N - 64 * s);
     T buf[2][RS][CB];

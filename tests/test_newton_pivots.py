@@ -1,7 +1,7 @@
 """Pivots of the blocked Newton path (N > 64): the search takes the largest
-magnitude by all its bits, and in mixed mode well-conditioned systems converge
-on the FP32 factor.  Sizes on both sides of each change of workgroup, panel and
-rows per lane.
+magnitude by all its bits, a pivot below the reciprocal's range is divided by,
+and in mixed mode well-conditioned systems converge on the FP32 factor.  Sizes
+on both sides of each change of workgroup, panel and rows per lane.
 """
 import numpy as np
 import pytest
@@ -46,6 +46,28 @@ def test_pivot_by_all_bits(N, mode):
     x, info = solve(N, A, b, mode)
     assert np.all(info == (0 if mode == 0 else -2)), info          # the largest double is inf in FP32
     assert np.max(np.abs(x - want)) <= 8 * U
+
+
+@pytest.mark.parametrize("N", [65, 129, 193, 257, 385, 513])
+@pytest.mark.parametrize("mode,exps", [(0, [-1021, -1023, -1024, -1025, -1030, -1050, -1070]),
+                                       (1, [-125, -127, -128, -129, -135, -140])])
+def test_last_pivot_below_the_reciprocals_range(N, mode, exps):
+    """The last pivot is 2^e, where 1 / 2^e can be inf; the right-hand side there
+    is 0 or 3 2^e, so every solution is exact: 0 or 3 there, 1 elsewhere.  In
+    mixed mode the residual's 1 - (1 - 3 2^e) loses 3 2^e, so that only the
+    systems with 0 converge on the FP32 factor."""
+    cases = [(e, y) for e in exps for y in (0.0, 3.0)]
+    i = N // 3
+    A = np.repeat(np.eye(N)[:, :, None], len(cases), axis=2)
+    b = np.ones((N, len(cases)))
+    want = np.ones((N, len(cases)))
+    for s, (e, y) in enumerate(cases):
+        A[i, i, s] = A[N - 1, N - 1, s] = 0.0
+        A[i, N - 1, s], A[N - 1, i, s] = 2.0 ** e, 1.0
+        b[i, s], want[N - 1, s] = y * 2.0 ** e, y
+    x, info = solve(N, A, b, mode)
+    assert np.array_equal(info, [0 if mode == 0 else 1 if y == 0 else -2 for _, y in cases]), info
+    assert np.array_equal(x, want)
 
 
 @pytest.mark.parametrize("N", [65, 96, 97, 128, 129, 192, 193, 256, 257, 384, 385, 512, 513, 608])
