@@ -4,10 +4,10 @@
 
 #include <cstdlib>
 #include <algorithm>
-#include <cmath>
 #include <cstring>
 #include <fstream>
 #include <mutex>
+#include <tuple>
 #include <sstream>
 #include <string>
 #include <vector>
@@ -57,7 +57,15 @@ struct pyjac_mech {
   size_t max_lds = 65536;
   pyjac::Variant jac_var, rates_var, conc_var;
   bool fixed[3] = {false, false, false};      // rates, Jacobian, concentration form: shape set or tuned
-  pyjac::Variant big[3];                      // shapes of large batches (big_shape)
+  pyjac::Variant big_rates;                   // rates_shape
+  // every shape that fits the Jacobian and the concentration form
+  struct Shape {
+    pyjac::Variant v;
+    int kpt;                                  // species per thread
+    double waves;                             // a workgroup's wavefronts, weighted by the groups that have species
+    int wgs;                                  // workgroups a CU holds
+  };
+  std::vector<Shape> shapes[2];
   int cus = 256;
   // gather lists by reaction-chunk size 16, 32, ..., 512 (threads / tile states)
   struct Lists {
@@ -177,41 +185,73 @@ bool fits(const pyjac_mech* m, int which, Variant v) {
 const int kShapes[][2] = {{16, 1024}, {16, 512}, {32, 1024}, {64, 1024}, {8, 512}, {8, 1024},
                           {4, 512},   {4, 1024}, {2, 512},   {2, 1024},  {8, 256}, {4, 256}};
 
-// Shape of a batch that fills the device, when none was set or tuned.
-// Rates: as many groups per state as the largest power of two in N (at least
-// 16), so that a species' gather has one group or two.  Jacobians: the most
-// wavefronts per CU (registers and LDS), weighted down by the groups that have
-// no species; the smaller workgroup wins a tie.  us per batch, this rule's
-// shape against the widest tile that fits: RHS 418 / 441 (53 species, 100,000
-// states), 222 / 253 (111, 20,001); Jacobian 141 / 315 (13, 100,000),
-// 1,297 / 1,531 (53, 100,000), 1,079 / 1,311 (80, 40,000), 1,269 / 1,263 (111,
-// 20,001), 1,603 / 1,603 (360, 2,051).
-Variant big_shape(const pyjac_mech* m, int which) {
-  const PackedMech& P = m->host;
-  Variant best{0, 0};
-  if (which == 0) {
-    int gr = 16;
-    while (2 * gr <= P.N && gr < 512) gr *= 2;
-    for (int nt : {512, 1024, 256})
-      for (auto& q : kShapes)
-        if (!best.ts && q[1] == nt && q[1] / q[0] == gr && fits(m, which, Variant{q[0], q[1]})) best = {q[0], q[1]};
-    return best;
-  }
-  double top = 0.0;
-  auto look = [&](int ts, int nt) {
+// Rates, when no shape was set or tuned and the batch gives every CU a tile: as
+// many groups per state as the largest power of two in N (at least 16), so
+// that a species' gather has one group or two.  us per batch, this shape
+// against the widest tile that fits: RHS 425 / 446 (53 species, 100,000
+// states), 226 / 258 (111, 20,001).
+Variant rates_shape(const pyjac_mech* m) {
+  int gr = 16;
+  while (2 * gr <= m->host.N && gr < 512) gr *= 2;
+  for (int nt : {512, 1024, 256})
+    for (auto& q : kShapes)
+      if (q[1] == nt && q[1] / q[0] == gr && fits(m, 0, Variant{q[0], q[1]})) return {q[0], q[1]};
+  return {0, 0};
+}
+
+// The shapes that jacobian_shape chooses from: two states per tile (16-byte
+// pieces of J) only where four with as many groups do not fit.  A wavefront
+// counts by the share of its shape's groups that have a species; with several
+// species per thread, by the mean of one and the share of the lanes in use.
+void list_shapes(pyjac_mech* m, int which) {
+  const int N = m->host.N;
+  auto add = [&](int ts, int nt) {
     const Variant v{ts, nt};
-    if (!fits(m, which, v)) return;
-    const int gr = nt / ts;
-    const int by_regs = (nt == 256 && P.N > gr ? 12 : 16) / (nt / 64), by_lds = (int)(163840 / kind_lds(m, which, v));
-    const double score = std::min(by_regs, by_lds) * (nt / 64) * std::sqrt(std::min(1.0, (double)P.N / gr));
-    if (score > 1.001 * top || (score > 0.999 * top && nt < best.nt)) {
-      top = score;
-      best = v;
-    }
+    if (!fits(m, which, v) || (ts == 2 && nt == 512 && fits(m, which, Variant{4, 1024}))) return;
+    const int gr = nt / ts, kpt = kpt_of(N, ts, nt), waves = nt / 64;
+    const int by_regs = (nt == 256 && kpt > 1 ? 12 : 16) / waves, by_lds = (int)(163840 / kind_lds(m, which, v));
+    const double fill = (double)N / (kpt * gr);
+    m->shapes[which - 1].push_back({v, kpt, waves * (kpt == 1 ? fill : 0.5 * (1.0 + fill)), std::min(by_regs, by_lds)});
   };
-  if (which == 1) for (auto& q : kShapes) look(q[0], q[1]);
-  else for (auto& q : kConcShapes) look(q[0], q[1]);
-  return best;
+  if (which == 1) for (auto& q : kShapes) add(q[0], q[1]);
+  else for (auto& q : kConcShapes) add(q[0], q[1]);
+}
+
+// Jacobian and concentration form, when no shape was set or tuned and the batch
+// gives every CU a tile: the most weighted wavefronts per CU, where a batch of
+// less than one round of resident workgroups counts the workgroups it has, and
+// one of less than two rounds pays for two.  Of shapes within 3 % one with the
+// fewest species per thread, then the smallest workgroup, then the widest
+// tile.  us per batch, this rule's shape against other candidates, Jacobian:
+//   13 species, 100,000 states   64 x 1024 144, 16 x 512 179, 16 x 1024 315
+//   53 species, 100,000 states   4 x 256 1,303, 8 x 512 1,253, 16 x 1024 1,383
+//   53 species,   3,000 states   4 x 256 61, 8 x 512 67, 16 x 1024 69
+//   80 species,  40,000 states   4 x 512 1,042, 8 x 1024 1,022, 4 x 256 1,179
+//   111 species, 20,001 states   4 x 256 1,125, 8 x 512 1,235, 4 x 1024 1,284, 2 x 512 1,423
+//   200 species,  7,000 states   4 x 1024 1,277, 2 x 512 1,273, 4 x 512 1,448
+//   360 species,  2,051 states   2 x 1024 1,605, 2 x 512 1,704
+// and concentration form:
+//   53 species, 100,000 states   4 x 256 1,403, 16 x 1024 1,302, 4 x 512 1,915
+//   111 species, 20,001 states   4 x 256 1,032, 8 x 512 1,099, 4 x 1024 1,207, 2 x 512 1,310
+//   200 species,  7,000 states   4 x 1024 530, 2 x 512 620, 4 x 512 705
+// Wavefronts weighted by the square root of the share took 2 x 512 at 111 and
+// 200 species, and without the batch's count 3,000 states of 13 species ran 64
+// to a tile (30 us, 23 with 8 x 256).
+Variant jacobian_shape(const pyjac_mech* m, int which, int64_t n) {
+  const auto& S = m->shapes[which - 1];
+  auto score = [&](const pyjac_mech::Shape& q) {
+    const double rounds = (double)((n + q.v.ts - 1) / q.v.ts) / (m->cus * q.wgs);
+    return q.waves * q.wgs * (rounds >= 2.0 ? 1.0 : rounds > 1.0 ? 0.5 * rounds : rounds);
+  };
+  double top = 0.0;
+  for (auto& q : S) top = std::max(top, score(q));
+  const pyjac_mech::Shape* best = nullptr;
+  for (auto& q : S) {
+    if (score(q) < 0.97 * top) continue;
+    auto key = [](const pyjac_mech::Shape& p) { return std::make_tuple(p.kpt, p.v.nt, -p.v.ts); };
+    if (!best || key(q) < key(*best)) best = &q;
+  }
+  return best ? best->v : Variant{0, 0};
 }
 
 // The shape of a call: the one set or tuned, otherwise by the batch.  A batch
@@ -238,7 +278,8 @@ Variant shape_for(const pyjac_mech* m, int which, int64_t n) {
     else for (auto& q : kShapes) look(q[0], q[1]);
     if (v.ts) return v;
   }
-  return m->big[which].ts ? m->big[which] : set;
+  const Variant v = which == 0 ? m->big_rates : jacobian_shape(m, which, n);
+  return v.ts ? v : set;
 }
 
 bool misaligned(const void* p) { return p && (reinterpret_cast<uintptr_t>(p) & 7u); }
@@ -300,7 +341,8 @@ pyjac_status pyjac_mech_load_string(const char* text, int32_t hip_device, pyjac_
   m->conc_var = pick_conc(m->host, m->max_lds);   // {0, 0}: the concentration form does not fit
   int cus = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, hip_device) == hipSuccess && cus > 0) m->cus = cus;
-  for (int w = 0; w < 3; ++w) m->big[w] = big_shape(m, w);
+  m->big_rates = rates_shape(m);
+  for (int w = 1; w < 3; ++w) list_shapes(m, w);
   *out = m;
   return PYJAC_OK;
 }
