@@ -356,7 +356,9 @@ pyjac_status pyjac_mech_autotune(pyjac_mech* mech, int32_t which, int64_t n_stat
                                  int32_t* n_entries, void* stream);
 
 /* Launch shape of a kernel family and its dynamic LDS bytes: the one set or
- * tuned, otherwise the one of work lists. */
+ * tuned.  Otherwise, for which = 0 and 2, the one in which a batch of many
+ * states runs (smaller batches choose their own), and for which = 1 the one of
+ * work lists (the shape their items need in common). */
 pyjac_status pyjac_mech_get_variant(const pyjac_mech* mech, int32_t which, int32_t* tile_states,
                                     int32_t* threads, size_t* lds_bytes);
 

@@ -720,7 +720,8 @@ pyjac_status pyjac_mech_autotune(pyjac_mech* m, int32_t which, int64_t n, int64_
 pyjac_status pyjac_mech_get_variant(const pyjac_mech* m, int32_t which, int32_t* ts, int32_t* nt,
                                     size_t* lds_bytes) {
   if (!m || which < 0 || which > 2) return fail(PYJAC_E_INVALID, "bad handle or kernel id");
-  const Variant v = which == 2 ? m->conc_var : which ? m->jac_var : m->rates_var;
+  // the Jacobian's is the shape that work lists need in common
+  const Variant v = which == 1 ? m->jac_var : shape_for(m, which, (int64_t)1 << 40);
   if (ts) *ts = v.ts;
   if (nt) *nt = v.nt;
   if (lds_bytes) *lds_bytes = v.ts ? kind_lds(m, which, v) : 0;

@@ -54,3 +54,21 @@ def test_chosen_shape(species, n, which, good):
     M = Mechanism(text=mechanism(species).to_text())
     shapes = launched_shapes(torch, calls_of(torch, M, n)[0][which])
     assert len(shapes) == 1 and shapes <= good
+
+
+@pytest.mark.parametrize("species,n", [(13, 100_000), (53, 30_000), (111, 20_001)])
+def test_reported_shape(species, n):
+    """get_variant names the shape that a large batch runs in (rates and
+    concentration form), the shape of work lists (Jacobian), and a set shape."""
+    import torch
+    from paper_1605_03262_amd import Mechanism, _lib
+    M = Mechanism(text=mechanism(species).to_text())
+    calls, phi, p, out = calls_of(torch, M, n)
+    for which in (0, 2):
+        assert launched_shapes(torch, calls[which]) == {M.get_variant(which)[:2]}, which
+    items = [(M.handle, n, n, phi.data_ptr(), p.data_ptr(), out.data_ptr())]
+    work_list = lambda: _lib.pyjac_eval_jacobian_multi(items, torch.cuda.current_stream().cuda_stream)  # noqa: E731
+    assert launched_shapes(torch, work_list) == {M.get_variant(1)[:2]}
+    for which, call in calls.items():
+        M.set_variant(which, 4, 512)
+        assert M.get_variant(which)[:2] == (4, 512) and launched_shapes(torch, call) == {(4, 512)}, which
