@@ -29,11 +29,16 @@ def torch():
     return t
 
 
-def parity(torch, mech, label):
+def parity(torch, mech, label, factor_tol=None):
+    """factor_tol: of the pressure factor alone, in place of the rates' own bars."""
     from oracle import RefMech
     ref, M = RefMech(text=mech.to_text()), gpu_mech(mech)
     phi, p = draw_states(77, mech.n_species, 37, T=(700.0, 2400.0), P_atm=(0.3, 80.0), dirichlet=0.5)
-    check_rates(gpu_rates(torch, M, phi, p, ld=41), ref.eval_rates(phi, p), mech, phi, p, label)
+    g, o = gpu_rates(torch, M, phi, p, ld=41), ref.eval_rates(phi, p)
+    if factor_tol is None:
+        check_rates(g, o, mech, phi, p, label)
+    else:
+        assert np.all(np.abs(g["pres_mod"] - o["pres_mod"]) <= factor_tol * o["pres_mod"] + 1e-300), label
     check_jac(gpu_jac(torch, M, phi, p, ld=41), ref.eval_jacobian(phi, p), label)
     c = conc_states(mech, phi, p)
     out, (colptr, rowidx) = gpu_conc(torch, M, c), M.conc_pattern()
@@ -52,6 +57,29 @@ def test_blending_terms_off(torch, oracle_built, kind):
         else:
             r.sri = par
         parity(torch, mech, f"{kind} {par}")
+
+
+@pytest.mark.parametrize("kind", ["falloff_troe", "chemact_troe", "falloff_sri", "chemact_sri"])
+@pytest.mark.parametrize("ratio", [1e-250, 1.0, 1e250])
+def test_logarithms_near_the_ends(torch, oracle_built, kind, ratio):
+    """log of F_cent or of the SRI base down to 1e-261, and of a reduced pressure
+    near 1e-250 and 1e250 (k_0 / k_inf scaled by it).  The factor is an exp of up
+    to 600 in magnitude, whose argument carries about 20 roundings on either
+    side: 600 * 40 * 2^-53 = 2.7e-12, bar 1e-11."""
+    mech = tiny(31, {kind: 1, "elementary": 2}, collider_probs=(0.5, 0.0))
+    r = next(q for q in mech.reactions if q.kind == kind)
+    scaled = (r.low if ratio < 1.0 else r.high)
+    scaled = (scaled[0] * min(ratio, 1.0 / ratio),) + tuple(scaled[1:])
+    if ratio < 1.0:
+        r.low = scaled
+    else:
+        r.high = scaled
+    for par in ((0.6, 1e-50, 4.0), (0.6, 1e-50, 40.0)) if "troe" in kind else ((0.5, 4e5, 1e-50), (0.5, 1e4, 1e-50)):
+        if "troe" in kind:
+            r.troe = par
+        else:
+            r.sri = par
+        parity(torch, mech, f"{kind} {ratio} {par}", factor_tol=1e-11)
 
 
 @pytest.mark.parametrize("kind,ta", [("elementary", 1e45), ("elementary", 1e50), ("elementary", 1e100),
