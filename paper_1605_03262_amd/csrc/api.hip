@@ -258,10 +258,11 @@ Variant jacobian_shape(const pyjac_mech* m, int which, int64_t n) {
 // too small to give every CU a tile takes the narrowest tiles that leave at
 // most one per CU, with enough threads for a group per reaction where the
 // shape is compiled, because its time is one tile's latency.  1,000 states of
-// 53 species: RHS 15 us (4 x 1,024) against 65 (64 x 1,024), Jacobian 31
-// against 60 (16 x 1,024); 500 of 111: 21 against 86 and 52 against 104.  Two
-// states per tile only where a chunk of 64 reactions is not all of them: 13
-// species run alike at every shape (15 to 18 us).
+// 53 species: RHS 13 us (4 x 1,024) against 64 (64 x 1,024), Jacobian 27 (4 x
+// 1,024) against 56 (16 x 1,024); 500 of 111, 2 x 1,024: RHS 18 against 44 (16
+// x 1,024), Jacobian 47 against 99 (8 x 512).  Two states per tile only where a
+// chunk of 64 reactions is not all of them: 48 states of 13 species take 12.5
+// to 14.5 us at every shape up to 16 states per tile.
 Variant shape_for(const pyjac_mech* m, int which, int64_t n) {
   const Variant set = which == 2 ? m->conc_var : which == 1 ? m->jac_var : m->rates_var;
   if (m->fixed[which]) return set;

@@ -41,7 +41,9 @@ struct alignas(16) RxnRec {
   int info, sum_f, sum_r, gslot;          // class/flags, sum nu', sum nu'', G slot or -1
   int mol[2 * kMaxSide];                  // reactant then product molecules (species index,
                                           // repeated per unit of nu); N = none (X[N] = 1)
-  int net[kMaxNet];                       // sp | nu << 16 (nu signed), -1 = none
+  int net[kMaxNet];                       // sp | nu << 16 (nu signed); unused entries follow the used ones
+                                          // and hold a species of the reaction with nu = 0 (always a
+                                          // valid index: the kernels read them without a condition)
   int coll_m, aux0, aux1, orig;           // collider species; efficiency or PLOG range or
                                           // Chebyshev offset; file index of the reaction
   double dnu_lnpr, alphaN_m1;             // sum(nu) ln(p_atm/R); alpha_N - 1
